@@ -21,7 +21,7 @@ namespace {
 constexpr size_t kAlign = 256;
 
 size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
-int ceil_div(int a, int b) { return (a + b - 1) / b; }
+int ceil_div(long long a, int b) { return (int)((a + b - 1) / b); }
 
 bool valid_r(int d, int r) { return r >= 1 && (r == d || (d % 2 == 0 && (d / 2) % r == 0)); }
 
@@ -152,6 +152,7 @@ struct SxShape {  // the fused step's selection + exact launch (sx_shape below)
     bool fits;       // within the kernel's limits
     bool one_round;  // every workgroup of the chosen form resident at once (one per CU)
     bool work;       // the one-selector form (below) is chosen
+    int wt;          // one-selector form: threads of a workgroup
     int P, web, wcb;  // one-selector form: workgroups per unit, exact blocks each, compensation blocks
                       // per worker
 };
@@ -234,7 +235,7 @@ SxShape sx_shape(const Geom& g, int nchunks, int K) {
     // tiles than the workgroup has waves takes several rounds of its waves), so that each CU streams
     // mean values while its item workgroup selects
     const size_t dyn = ((size_t)2 * (nchunks + 1) * g.G + (size_t)xmax) * sizeof(float);
-    const int resident = compkv::select_exact_slots(g, dyn);
+    const int resident = compkv::select_exact_slots(g, dyn, 1024);
     const int per = std::max(1, resident / std::max(1, g.units()));
     const int cbmax = compkv::select_exact_max_cb();
     int n_comp = std::max(1, std::min(per / 2, ceil_div(xmax, 128)));
@@ -248,13 +249,23 @@ SxShape sx_shape(const Geom& g, int nchunks, int K) {
                       n_comp + n_exact <= compkv::decode_max_partials() &&
                       (n_comp + n_exact) * g.G <= compkv::select_exact_merge_terms();
     // one-selector launch: per unit one selector and P - 1 workers, compensation shares of at least 128
-    // blocks, every workgroup resident at once
-    int P = std::min(per, 1 + ceil_div(xmax, 128));
+    // blocks, every workgroup resident at once. Workgroups of 1024 threads, one per CU; where these would
+    // be fewer than two per unit (more than half as many units as CUs), of 512 threads, two per CU, so
+    // that a unit keeps its worker and one workgroup's loads overlap the other's selection (256 units of up
+    // to 8K tokens: 61 us a step against 78 for the four separate launches; 160 units 51 against 59; with
+    // two 1024-thread workgroups per unit the larger form stays better at long contexts: 128 units of 16K
+    // 54 against 56 us but 32 units of 128K 49 against 46). Its selection holds at most
+    // 16 keys per thread (4 with logit terms).
+    const bool small = 2 * g.units() > resident && (g.G != 8 || xmax <= 2048);
+    const int wt = small ? 512 : 1024;
+    const int wresident = small ? compkv::select_exact_slots(g, dyn, wt) : resident;
+    const int wper = std::max(1, wresident / std::max(1, g.units()));
+    int P = std::min(wper, std::max(1 + ceil_div(xmax, 128), small ? ceil_div((long long)keff * g.B, 256) : 0));
     P = std::max(P, 1 + ceil_div(xmax, cbmax));
     P = std::max(P, ceil_div(keff, compkv::decode_max_eb()));
     const int wcb = ceil_div(xmax, std::max(1, P - 1));
     const int web = ceil_div(keff, P);
-    const bool work_fits = cus > 0 && P >= 2 && (long long)g.units() * P <= resident &&
+    const bool work_fits = cus > 0 && P >= 2 && (long long)g.units() * P <= wresident &&
                            K <= compkv::select_exact_max_budget() && xmax <= 8192 && dyn <= 32768 &&
                            web <= compkv::decode_max_eb() && wcb <= cbmax &&
                            P * g.G <= compkv::select_exact_merge_terms();
@@ -265,7 +276,7 @@ SxShape sx_shape(const Geom& g, int nchunks, int K) {
     // stream from the start while the item workgroups select is faster (measured: 128K layer 26.9 vs
     // 28.6 us; wide GQA 33.3 vs 29.9 us; 32K layer 18.3 vs 18.5 us)
     const bool work = work_fits && ((long long)xmax <= (long long)keff * g.B || !items_round);
-    return {eb, n_exact, cb, n_comp, fits, work || items_round, work, P, web, wcb};
+    return {eb, n_exact, cb, n_comp, fits, work || items_round, work, wt, P, web, wcb};
 }
 
 // Shape of the two-launch step: the chunked path's scoring chunks; one round of selectors and
@@ -755,7 +766,7 @@ int compkv_decode_step(const compkv_dims* dims, const compkv_select_params* para
         d.timeouts = state;
         d.trace = g_trace_fused;
         a.trace = g_trace_fused;  // (the selection's marks, in the fused launch's records)
-        if (work) return launch_status(compkv::launch_select_work(g, a, d, sx.P, s));
+        if (work) return launch_status(compkv::launch_select_work(g, a, d, sx.P, sx.wt, s));
         return launch_status(compkv::launch_select_exact(g, a, d, sx.n_exact, s));
     }
     // separate selection and exact items. Mean: the chunks' compensation partials, then the exact

@@ -186,11 +186,11 @@ hipError_t launch_select_exact(const Geom& g, ScoreArgs a, const DecodeArgs& d, 
 // d.eb once the selection word is set): P workgroups per unit, all resident at once (checked by the
 // caller with select_exact_slots); one partial per workgroup (d.part_count = P, d.part_base = 0: a
 // worker's compensation partial joins its exact one); hipErrorInvalidValue outside its limits
-hipError_t launch_select_work(const Geom& g, ScoreArgs a, const DecodeArgs& d, int P, hipStream_t s);
+hipError_t launch_select_work(const Geom& g, ScoreArgs a, const DecodeArgs& d, int P, int threads, hipStream_t s);
 int select_exact_max_budget();
 int select_exact_waves();
 int select_exact_max_cb();  // blocks per compensation workgroup of the fused launch
-int select_exact_slots(const Geom& g, size_t dyn);  // one-selector launch: workgroups resident at once
+int select_exact_slots(const Geom& g, size_t dyn, int threads);  // one-selector launch: workgroups resident at once
 int select_exact_merge_terms();  // partials x heads limit of its in-launch merge
 hipError_t launch_decode_merge(const Geom& g, const DecodeArgs& a, int nitems, hipStream_t s);
 

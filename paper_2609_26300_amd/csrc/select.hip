@@ -247,12 +247,28 @@ __global__ __launch_bounds__(kThreads) void score_chunks_kernel(Geom geo, ScoreA
     const float logB = logf((float)geo.B);
     __syncthreads();
     COMPKV_MARK(a.trace, 2);  // the query in LDS
+    // a chunk past the sequence's full blocks (workgroup-uniform): neutral partials, nothing read (with the
+    // clamp below, ragged batches no longer read the longest sequence's blocks for every unit: 256 units of
+    // 1K-8K tokens, this launch 18.6 -> 15.0 us)
+    if (chunk0 >= xs) {
+        float* pp = a.ws_part + ((size_t)u * (a.nchunks + 1) + chunk) * G * 2;
+        for (int g = tid; g < G; g += kThreads) {
+            pp[2 * g] = -INFINITY;
+            pp[2 * g + 1] = 0.0f;
+        }
+        if (comp) {
+            float* cp = a.comp_part + ((size_t)u * a.part_count + chunk) * G * (D + 2);
+            for (int idx = tid; idx < G * (D + 2); idx += kThreads) cp[idx] = (idx % (D + 2) == 0) ? -INFINITY : 0.0f;
+        }
+        COMPKV_TRACE_END(a.trace);
+        return;
+    }
     // a rolling window of two slots: slot p + 2 is requested once slot p is computed
     float4 kv[2][NF4];
     float dv0[2];
     auto issue = [&](int p, int w) {
         const int b = chunk0 + p * 32 + grp;
-        const size_t blk = (size_t)u * geo.xcap + (b < xmax ? b : 0);
+        const size_t blk = (size_t)u * geo.xcap + (b < xs ? b : chunk0);
         const float4* kp = reinterpret_cast<const float4*>(a.kmean + blk * D);
 #pragma unroll
         for (int m = 0; m < NF4; ++m) kv[w][m] = kp[li + 8 * m];
@@ -323,7 +339,7 @@ __global__ __launch_bounds__(kThreads) void score_chunks_kernel(Geom geo, ScoreA
 #pragma unroll
         for (int k = 0; k < VROWS; ++k) {
             const int b = chunk0 + vslot + k * RPS;
-            vrow[k] = vm[(size_t)(b < xmax ? b : 0) * (D / 4)];
+            vrow[k] = vm[(size_t)(b < xs ? b : chunk0) * (D / 4)];
         }
     }
     __syncthreads();
@@ -662,6 +678,9 @@ constexpr int kSxKeys = 8192 / kSxThreads;
 // d = 128). While nearly every CU streams, that suffices for the HBM rate, and less data queued at the
 // memory keeps the latency of the selections' and the exact items' loads short.
 constexpr int kCompRows = 1;
+// the same in the 512-thread form, where one or two workers per unit stream the mean values (64 KB in flight
+// each): 256 units of up to 8K tokens, fused launch 43.1 us against 45.0 with one row
+constexpr int kCompRowsSmall = 4;
 
 // Exact attention of unit u over nblk selected blocks whose ids are in LDS (ids; -1 or an id past the
 // unit's blocks contributes nothing) into decode partial `part` of the unit (device-coherent stores).
@@ -767,10 +786,10 @@ constexpr uint32_t kPosted = 0x80000000u;  // mailbox value of id b: b ^ kPosted
 constexpr uint32_t kSelFailed = 1u;        // selection word: a worker's wait timed out
 constexpr int kSelSpinLimit = 1 << 17;     // polls of a wait (each a memory round trip): well over 50 ms
 
-// KPT: keys per thread of the selection (xmax <= KPT kSxThreads); kLogits: a.logit_terms
-template <int D, int G, int KPT, bool kLogits = false>
-__global__ __launch_bounds__(kSxThreads) void select_work_kernel(Geom geo, ScoreArgs a, DecodeArgs d, int P) {
-    constexpr int FT = kSxThreads, NW = FT / 64;
+// FT: threads, 1024 (one workgroup per CU) or 512 (two per CU: many units, chosen by the host); KPT: keys per thread of the selection (xmax <= KPT FT); kLogits: a.logit_terms
+template <int D, int G, int FT, int KPT, bool kLogits = false>
+__global__ __launch_bounds__(FT) void select_work_kernel(Geom geo, ScoreArgs a, DecodeArgs d, int P) {
+    constexpr int NW = FT / 64;
     using Lds = SelExactLdsT<D, G, kStepCbMax, NW>;
     __shared__ Lds L;
     extern __shared__ float dyn[];
@@ -808,11 +827,16 @@ __global__ __launch_bounds__(kSxThreads) void select_work_kernel(Geom geo, Score
         auto request = [&] { mv = ld_agent_u32(mbox + (tid < nblk ? e0 + tid : 0)); };
         const bool comp = d.n_comp > 0;  // (workgroup-uniform)
         if (comp) {  // its compensation partial stays in LDS for the exact partial to absorb
-            const int xmax = geo.xmax();
-            const int c0 = min((w - 1) * d.cb, xmax), c1 = min(c0 + d.cb, xmax);
+            // the 512-thread form is bound by the bytes of many short sequences: equal shares of the
+            // sequence's own blocks (ragged lengths: 74 -> 60 us a step at 256 units of 1K-8K tokens).
+            // The 1024-thread form is bound by latency: shares of the longest sequence, whose rows are
+            // requested without waiting for the length
+            const int X = FT < 1024 ? (clamp_len(n_raw, geo.max_seq) + geo.B - 1) / geo.B : geo.xmax();
+            const int cb = FT < 1024 ? (X + d.n_comp - 1) / d.n_comp : d.cb;
+            const int c0 = min((w - 1) * cb, X), c1 = min(c0 + cb, X);
             // the slots are polled once the last mean values are requested: if the selector has posted
             // them by then, they return with those values; else they are requested once more after them
-            step_compensation<D, G, kCompRows, Lds, FT, true>(
+            step_compensation<D, G, (FT < 1024 ? kCompRowsSmall : kCompRows), Lds, FT, true>(
                 geo, d, u, n_raw, c0, c1, L, nullptr, [&] { if (__any(mv == 0u)) request(); }, request);
         } else {
             request();
@@ -919,36 +943,40 @@ hipError_t launch_sx(const Geom& g, const ScoreArgs& a, const DecodeArgs& d, int
     return hipGetLastError();
 }
 
-template <int D, int G>
+template <int D, int G, int FT>
 hipError_t launch_work(const Geom& g, const ScoreArgs& a, const DecodeArgs& d, int P, hipStream_t s) {
     const dim3 grid(P * g.units());
     const size_t dyn = finalize_dyn_lds(g, a);
     if constexpr (G >= 4) {
-        if (a.logit_terms) {  // (at most 4096 blocks: checked by the launcher)
-            if (g.xmax() <= kSxThreads)
-                select_work_kernel<D, G, 1, true><<<grid, kSxThreads, dyn, s>>>(g, a, d, P);
+        if (a.logit_terms) {  // (at most 4 FT blocks: checked by the launcher)
+            if (g.xmax() <= FT)
+                select_work_kernel<D, G, FT, 1, true><<<grid, FT, dyn, s>>>(g, a, d, P);
+            else if (FT < 1024 && g.xmax() <= 2 * FT)
+                select_work_kernel<D, G, FT, FT < 1024 ? 2 : 4, true><<<grid, FT, dyn, s>>>(g, a, d, P);
             else
-                select_work_kernel<D, G, 4, true><<<grid, kSxThreads, dyn, s>>>(g, a, d, P);
+                select_work_kernel<D, G, FT, 4, true><<<grid, FT, dyn, s>>>(g, a, d, P);
             return hipGetLastError();
         }
     }
     // keys per thread for the unit's blocks: fewer loads and keys where the blocks are few
-    if (g.xmax() <= kSxThreads)
-        select_work_kernel<D, G, 1><<<grid, kSxThreads, dyn, s>>>(g, a, d, P);
-    else if (g.xmax() <= 4 * kSxThreads)
-        select_work_kernel<D, G, 4><<<grid, kSxThreads, dyn, s>>>(g, a, d, P);
+    if (g.xmax() <= FT)
+        select_work_kernel<D, G, FT, 1><<<grid, FT, dyn, s>>>(g, a, d, P);
+    else if (FT < 1024 && g.xmax() <= 2 * FT)
+        select_work_kernel<D, G, FT, FT < 1024 ? 2 : 4><<<grid, FT, dyn, s>>>(g, a, d, P);
+    else if (g.xmax() <= 4 * FT)
+        select_work_kernel<D, G, FT, 4><<<grid, FT, dyn, s>>>(g, a, d, P);
     else
-        select_work_kernel<D, G, kSxKeys><<<grid, kSxThreads, dyn, s>>>(g, a, d, P);
+        select_work_kernel<D, G, FT, 8192 / FT><<<grid, FT, dyn, s>>>(g, a, d, P);
     return hipGetLastError();
 }
 
-template <int D>
+template <int D, int FT>
 hipError_t work_g(const Geom& g, const ScoreArgs& a, const DecodeArgs& d, int P, hipStream_t s) {
     switch (g.G) {
-        case 1: return launch_work<D, 1>(g, a, d, P, s);
-        case 2: return launch_work<D, 2>(g, a, d, P, s);
-        case 4: return launch_work<D, 4>(g, a, d, P, s);
-        case 8: return launch_work<D, 8>(g, a, d, P, s);
+        case 1: return launch_work<D, 1, FT>(g, a, d, P, s);
+        case 2: return launch_work<D, 2, FT>(g, a, d, P, s);
+        case 4: return launch_work<D, 4, FT>(g, a, d, P, s);
+        case 8: return launch_work<D, 8, FT>(g, a, d, P, s);
         default: return hipErrorInvalidValue;
     }
 }
@@ -975,24 +1003,29 @@ int select_exact_merge_terms() { return kMergeMaxTerms; }
 // Resident workgroups of the one-selector fused launch on the current device with `dyn` bytes of
 // dynamic LDS each.
 template <int D, int G>
-int sx_slots(size_t dyn) {
+int sx_slots(size_t dyn, int threads) {
     int per_cu = 0, cus = 0, dev = 0;
     if (hipGetDevice(&dev) != hipSuccess ||
-        hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, select_work_kernel<D, G, kSxKeys>, kSxThreads, dyn) != hipSuccess ||
+        (threads == kSxThreads
+             ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, select_work_kernel<D, G, 1024, 8>, 1024, dyn)
+             : hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, select_work_kernel<D, G, 512, 16>, 512, dyn)) !=
+            hipSuccess ||
         hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
         return 0;
     return per_cu * cus;
 }
 template <int D>
-int sx_slots_d(const Geom& g, size_t dyn) {
+int sx_slots_d(const Geom& g, size_t dyn, int threads) {
     switch (g.G) {
-        case 1: return sx_slots<D, 1>(dyn);
-        case 2: return sx_slots<D, 2>(dyn);
-        case 4: return sx_slots<D, 4>(dyn);
-        default: return sx_slots<D, 8>(dyn);
+        case 1: return sx_slots<D, 1>(dyn, threads);
+        case 2: return sx_slots<D, 2>(dyn, threads);
+        case 4: return sx_slots<D, 4>(dyn, threads);
+        default: return sx_slots<D, 8>(dyn, threads);
     }
 }
-int select_exact_slots(const Geom& g, size_t dyn) { return g.D == 128 ? sx_slots_d<128>(g, dyn) : sx_slots_d<64>(g, dyn); }
+int select_exact_slots(const Geom& g, size_t dyn, int threads) {
+    return g.D == 128 ? sx_slots_d<128>(g, dyn, threads) : sx_slots_d<64>(g, dyn, threads);
+}
 
 // the selection's logit-terms input (ScoreArgs::logit_terms) within its limits
 bool logit_terms_ok(const Geom& g, const ScoreArgs& a) {
@@ -1011,7 +1044,7 @@ hipError_t launch_select_exact(const Geom& g, ScoreArgs a, const DecodeArgs& d, 
         return hipErrorInvalidValue;
     return g.D == 128 ? sx_g<128>(g, a, d, items, s) : sx_g<64>(g, a, d, items, s);
 }
-hipError_t launch_select_work(const Geom& g, ScoreArgs a, const DecodeArgs& d, int P, hipStream_t s) {
+hipError_t launch_select_work(const Geom& g, ScoreArgs a, const DecodeArgs& d, int P, int threads, hipStream_t s) {
     a.keys_in_lds = 1;
     if (!logit_terms_ok(g, a)) return hipErrorInvalidValue;
     const int keff = std::max(1, std::min(a.K, g.xmax()));
@@ -1020,7 +1053,12 @@ hipError_t launch_select_work(const Geom& g, ScoreArgs a, const DecodeArgs& d, i
         (d.n_comp != 0 && (d.n_comp != P - 1 || d.cb < 1 || d.cb > kStepCbMax || (long long)d.n_comp * d.cb < g.xmax())) ||
         d.part_base != 0 || d.part_count != P || d.part_count * g.G > kMergeMaxTerms)
         return hipErrorInvalidValue;
-    return g.D == 128 ? work_g<128>(g, a, d, P, s) : work_g<64>(g, a, d, P, s);
+    if (threads == 512) {
+        if (a.logit_terms && g.xmax() > 4 * threads) return hipErrorInvalidValue;
+        return g.D == 128 ? work_g<128, 512>(g, a, d, P, s) : work_g<64, 512>(g, a, d, P, s);
+    }
+    if (threads != kSxThreads) return hipErrorInvalidValue;
+    return g.D == 128 ? work_g<128, 1024>(g, a, d, P, s) : work_g<64, 1024>(g, a, d, P, s);
 }
 int select_one_group_terms() { return kUnitTerms; }
 int select_one_group_auto_blocks() { return kUnitBatch * kFinThreads / 8; }

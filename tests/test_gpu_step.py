@@ -242,3 +242,28 @@ def test_step_stays_within_workspace(name, path):
     assert bool((buf[:state] == 0).all()), "the step left its per-unit words non-zero"
     for k in ref:
         assert torch.equal(r[k], ref[k]), k
+
+
+# more than half as many units as compute units: the fused launch's 512-thread form (two or three workgroups
+# per unit), on lengths from empty to full, with a budget above the shortest sequences' blocks; 16 query
+# heads on one KV head pair d = 64 (G = 8), and unit counts that do not fill whole rounds of eight
+@pytest.mark.parametrize("batch,heads,d,B,context,budget", [(65, (8, 2), 128, 16, 1030, 12), (70, (16, 2), 64, 48, 2500, 20),
+                                                            (129, (1, 1), 128, 1, 700, 130), (128, (4, 2), 128, 32, 900, 9)])
+def test_step_many_units(batch, heads, d, B, context, budget):
+    lens = [context, 0, 1, B, B + 1, context - 1] + [1 + (37 * i) % context for i in range(6, batch)]
+    c = Case(TINY.with_(batch=batch, n_q_heads=heads[0], n_kv_heads=heads[1], head_dim=d, block_size=B, context=context,
+                        budget_blocks=budget, seed=61), seq_lens=lens)
+    c.run_all()
+    c.select_path = P.COMPKV_SELECT_CHUNKED
+    ref = c.decode_step()
+    c.select_path = P.COMPKV_SELECT_AUTO
+    assert P.compkv_decode_step_path(c.dims, c.params()) == P.COMPKV_SELECT_CHUNKED_EXACT
+    K2, V2, kn, vn, summ2 = _prefix_state(c)
+    got = c.decode_step(kn, vn, summ=summ2, K=K2, V=V2)
+    torch.cuda.synchronize()
+    assert torch.equal(K2, c.K) and torch.equal(V2, c.V)
+    for k in ("kmean", "dvar", "vmean"):
+        assert torch.equal(getattr(summ2, k), getattr(c.summ, k)), k
+    for k in ("sel", "n_sel", "blk_logit", "scores"):
+        assert torch.equal(got[k], ref[k]), k
+    _oracle_end_to_end(c, got)
