@@ -9,7 +9,9 @@ namespace compkv {
 
 template <int D>
 struct BlockStatsLds {
-    float part[4][2][D];  // per-wave partial sums (key, value), later (squared deviations)
+    // partial sums of each row group of each wave (4 waves of 64 / (d/8) groups): key, value; later the
+    // squared deviations in the key's place
+    alignas(16) float part[4][64 / (D / 8)][2][D];
     alignas(16) float km[D];
     alignas(16) float vm[D];
     float dv[D];
@@ -21,8 +23,10 @@ struct BlockStatsLds {
 //
 // A row of d bf16 is d/8 lanes x 16 bytes; a wave covers 64/(d/8) rows per load step and the workgroup
 // four times that. Wave w takes rows 16s + 4w + (lane / 16) (for d = 128) of each step s, up to four
-// steps per batch with every load of a batch issued before use. Per-lane sums over the rows, then
-// cross-lane sums within the wave, then the four waves in a fixed order. Two passes (mean, then
+// steps per batch with every load of a batch issued before use. Per-lane sums over the rows, then the
+// four waves' sums of each row group ((w0 + w1) + (w2 + w3)), then the row groups pairwise
+// ((g0 + g1) + (g2 + g3), ...): the order in which one wave that plays all four (wave_block_stats) needs
+// a single butterfly over its lanes instead of one per wave played. Two passes (mean, then
 // squared deviations from the mean) keep the variance stable; a block of at most one batch per wave
 // (64 rows for d = 128) is still in registers for the second pass. On return the results are written
 // to km_out / vm_out / dv_out and their copies in L.km / L.vm / L.dv are visible to the workgroup.
@@ -72,6 +76,26 @@ __device__ __forceinline__ void load_block_rows(const BlockSrc& b, int s0, Block
     }
 }
 
+__device__ __forceinline__ void store_group_sums(float* p, const float (&x)[8]) {
+    reinterpret_cast<float4*>(p)[0] = make_float4(x[0], x[1], x[2], x[3]);
+    reinterpret_cast<float4*>(p)[1] = make_float4(x[4], x[5], x[6], x[7]);
+}
+
+// total of coordinate c over the waves, then over the row groups (the order stated above)
+template <int D>
+__device__ __forceinline__ float group_sum(const BlockStatsLds<D>& L, int which, int c) {
+    constexpr int RPW = 64 / (D / 8);
+    float t[RPW];
+#pragma unroll
+    for (int g = 0; g < RPW; ++g)
+        t[g] = (L.part[0][g][which][c] + L.part[1][g][which][c]) + (L.part[2][g][which][c] + L.part[3][g][which][c]);
+#pragma unroll
+    for (int h = 1; h < RPW; h <<= 1)
+#pragma unroll
+        for (int g = 0; g < RPW; g += 2 * h) t[g] = t[g] + t[g + h];
+    return t[0];
+}
+
 // The summary from the rows of the first batch (already requested into R) and the rest of the block.
 // In a workgroup larger than four waves only waves 0-3 work (`active`); every thread reaches the
 // barriers.
@@ -105,30 +129,16 @@ __device__ void block_stats_from(const BlockSrc& b, BlockRows& R, int r, int lay
         }
     }
     if (active) {
-#pragma unroll
-        for (int off = LPR; off < 64; off <<= 1)
-#pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                sk[e] = xor_add(sk[e], off);
-                sv[e] = xor_add(sv[e], off);
-            }
-    }
-    if (active && ro == 0) {
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            L.part[wave][0][li * 8 + e] = sk[e];
-            L.part[wave][1][li * 8 + e] = sv[e];
-        }
+        store_group_sums(&L.part[wave][ro][0][li * 8], sk);
+        store_group_sums(&L.part[wave][ro][1][li * 8], sv);
     }
     __syncthreads();
     const float fn = (float)nb;
-    for (int i = tid; i < D; i += kThreads) {
-        const float mk = ((L.part[0][0][i] + L.part[1][0][i]) + (L.part[2][0][i] + L.part[3][0][i])) / fn;
-        const float mv = ((L.part[0][1][i] + L.part[1][1][i]) + (L.part[2][1][i] + L.part[3][1][i])) / fn;
-        L.km[i] = mk;
-        L.vm[i] = mv;
-        km_out[i] = mk;
-        vm_out[i] = mv;
+    for (int i = tid; i < 2 * D; i += kThreads) {  // (threads below 256: the key's means, then the value's)
+        const int which = i / D, c = i - which * D;
+        const float mean = group_sum<D>(L, which, c) / fn;
+        (which ? L.vm : L.km)[c] = mean;
+        (which ? vm_out : km_out)[c] = mean;
     }
     __syncthreads();
     float mk[8], m2[8];
@@ -151,18 +161,9 @@ __device__ void block_stats_from(const BlockSrc& b, BlockRows& R, int r, int lay
             }
         }
     }
-    if (active) {
-#pragma unroll
-        for (int off = LPR; off < 64; off <<= 1)
-#pragma unroll
-            for (int e = 0; e < 8; ++e) m2[e] = xor_add(m2[e], off);
-    }
-    if (active && ro == 0) {
-#pragma unroll
-        for (int e = 0; e < 8; ++e) L.part[wave][0][li * 8 + e] = m2[e];
-    }
+    if (active) store_group_sums(&L.part[wave][ro][0][li * 8], m2);
     __syncthreads();
-    auto m2_of = [&](int i) { return (L.part[0][0][i] + L.part[1][0][i]) + (L.part[2][0][i] + L.part[3][0][i]); };
+    auto m2_of = [&](int i) { return group_sum<D>(L, 0, i); };
     if (r == D) {
         for (int t = tid; t < D; t += kThreads) {
             const float dv = m2_of(t) / fn;
@@ -186,121 +187,119 @@ __device__ void block_stats_from(const BlockSrc& b, BlockRows& R, int r, int lay
     __syncthreads();
 }
 
-// The same summary computed by ONE wave (no barrier, no LDS), for blocks of at most two workgroup load
-// steps (nb <= 2 * 4 * 64/(d/8): 32 rows at d = 128, 64 at d = 64). The wave plays the four waves of the
-// workgroup routine in turn (virtual wave v takes the rows the real wave v takes there) and adds in
-// exactly the same order: per lane over the steps, the butterflies over the row groups, the four waves'
-// sums as (w0 + w1) + (w2 + w3), the pair sums and the group butterflies over lanes = pairs. So its
-// results are bit-identical to block_stats_from's, which the append and the fused step keep using.
+// The same summary computed by ONE wave (no barrier, no LDS) for blocks of at most NS workgroup load
+// steps (NS * 4 * 64/(d/8) rows). The wave plays the four waves of the workgroup routine (virtual wave v
+// takes the rows the real wave v takes there) and adds in exactly the same order: per lane over the steps,
+// the four waves' sums, the butterflies over the row groups, the pair sums and the group butterflies over
+// lanes = pairs. So its results are bit-identical to block_stats_from's, which the append and the fused
+// step keep using.
+constexpr int kWaveStepsMax = 4;
 template <int D>
-constexpr int wave_stats_max_rows() {
-    return 2 * 4 * (64 / (D / 8));
+constexpr int wave_stats_max_rows(int steps) {
+    return steps * 4 * (64 / (D / 8));
 }
 
-template <int D>
-__device__ void wave_block_stats(const BlockSrc& b, int r, int layout, float* __restrict__ km_out,
-                                 float* __restrict__ dv_out, float* __restrict__ vm_out) {
-    constexpr int LPR = D / 8;     // lanes per row
-    constexpr int RPW = 64 / LPR;  // rows per wave step
-    constexpr int RPG = 4 * RPW;   // rows per workgroup step
+// The rows of one of the block's two arrays held by a wave: [step][virtual wave]
+template <int NS>
+struct WaveRows {
+    uint4 w[NS][4];
+};
+
+// Requests steps [s0, s0 + NS) of a block of nb rows at p (branch-free: rows past the block reload row 0)
+template <int D, int NS>
+__device__ __forceinline__ void load_wave_rows(const uint16_t* p, int nb, int s0, WaveRows<NS>& R) {
+    constexpr int LPR = D / 8, RPW = 64 / LPR, RPG = 4 * RPW;
     const int lane = threadIdx.x & 63, ro = lane / LPR, li = lane % LPR;
-    const int nb = b.nb;
-    // every row of the block (two workgroup steps x four virtual waves), requested at once
-    uint4 kw[2][4], vw[2][4];
 #pragma unroll
-    for (int st = 0; st < 2; ++st)
+    for (int st = 0; st < NS; ++st)
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
-            const int j = st * RPG + v * RPW + ro;
-            const int jj = j < nb ? j : 0;
-            kw[st][v] = *reinterpret_cast<const uint4*>(stats_krow<D>(b, jj) + li * 8);
-            vw[st][v] = *reinterpret_cast<const uint4*>(stats_vrow<D>(b, jj) + li * 8);
+            const int j = (s0 + st) * RPG + v * RPW + ro;
+            // (a wave-uniform base and a 32-bit byte offset)
+            const unsigned off = (unsigned)(j < nb ? j : 0) * (2 * D) + li * 16;
+            R.w[st][v] = load_once(reinterpret_cast<const char*>(p) + off);
         }
-    // per virtual wave: the lane's sums over its rows (step order), then over the row groups
-    float tk[8], tv[8], ak[8], av[8];
+}
+
+// x / n for a wave-uniform count n: for a power of two the product with its exact reciprocal, the same bits
+__device__ __forceinline__ void divide8(float (&x)[8], int n) {
+    if ((n & (n - 1)) == 0) {
+        const float inv = 1.0f / (float)n;
 #pragma unroll
-    for (int v = 0; v < 4; ++v) {
-        float sk[8] = {0, 0, 0, 0, 0, 0, 0, 0}, sv[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+        for (int e = 0; e < 8; ++e) x[e] *= inv;
+    } else {
+        const float fn = (float)n;
 #pragma unroll
-        for (int st = 0; st < 2; ++st) {
-            const bool ok = st * RPG + v * RPW + ro < nb;
-            float kf[8], vf[8];
-            unpack_bf16x8(kw[st][v], kf);
-            unpack_bf16x8(vw[st][v], vf);
-#pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                sk[e] += ok ? kf[e] : 0.0f;
-                sv[e] += ok ? vf[e] : 0.0f;
-            }
-        }
-        // (the workgroup routine's later steps add +0 for rows past the block: no change)
-#pragma unroll
-        for (int off = LPR; off < 64; off <<= 1)
-#pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                sk[e] = xor_add(sk[e], off);
-                sv[e] = xor_add(sv[e], off);
-            }
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            if (v == 0 || v == 2) {
-                tk[e] = sk[e];
-                tv[e] = sv[e];
-            } else if (v == 1) {
-                ak[e] = tk[e] + sk[e];
-                av[e] = tv[e] + sv[e];
-            } else {
-                ak[e] = ak[e] + (tk[e] + sk[e]);
-                av[e] = av[e] + (tv[e] + sv[e]);
-            }
-        }
+        for (int e = 0; e < 8; ++e) x[e] /= fn;
     }
+}
+
+// Keeps the compiler from carrying the rows' unpacked values (four times the registers) past this point
+template <int NS>
+__device__ __forceinline__ void pin_rows(WaveRows<NS>& R) {
+#pragma unroll
+    for (int st = 0; st < NS; ++st)
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+            __asm__ volatile("" : "+v"(R.w[st][v].x), "+v"(R.w[st][v].y), "+v"(R.w[st][v].z), "+v"(R.w[st][v].w));
+}
+
+// Adds the rows to the lane's per-virtual-wave sums s[v][8] (kDev: the squared deviations from mk instead).
+// A row past the block (a reload of row 0) enters with factor 0: fma(1, x, s) rounds like s + x, so the mask
+// costs one instruction per row instead of one per value, and no second code path.
+template <int D, int NS, bool kDev>
+__device__ __forceinline__ void add_wave_rows(const WaveRows<NS>& R, int nb, int s0, const float (&mk)[8], float (&s)[4][8]) {
+    constexpr int LPR = D / 8, RPW = 64 / LPR, RPG = 4 * RPW;
+    const int ro = (threadIdx.x & 63) / LPR;
+#pragma unroll
+    for (int st = 0; st < NS; ++st)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const float in = (s0 + st) * RPG + v * RPW + ro < nb ? 1.0f : 0.0f;
+            float f[8];
+            unpack_bf16x8(R.w[st][v], f);
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                float x = f[e];
+                if constexpr (kDev) {
+                    const float dev = f[e] - mk[e];
+                    x = __fmul_rn(dev, dev);
+                }
+                s[v][e] = __builtin_fmaf(in, x, s[v][e]);
+            }
+        }
+}
+
+// ((w0 + w1) + (w2 + w3)), then over the row groups: every lane of a column holds the column's total
+template <int D>
+__device__ __forceinline__ void total_wave_rows(const float (&s)[4][8], float (&t)[8]) {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) t[e] = (s[0][e] + s[1][e]) + (s[2][e] + s[3][e]);
+#pragma unroll
+    for (int off = D / 8; off < 64; off <<= 1)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) t[e] = xor_add(t[e], off);
+}
+
+__device__ __forceinline__ void zero_sums(float (&s)[4][8]) {
+#pragma unroll
+    for (int v = 0; v < 4; ++v)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) s[v][e] = 0.0f;
+}
+
+// The grouped variances from the coordinates' sums of squared deviations m2 (lane li: 8 li .. 8 li + 7)
+template <int D>
+__device__ __forceinline__ void store_wave_variances(float (&m2)[8], int nb, int r, int layout,
+                                                     float* __restrict__ dv_out) {
+    constexpr int LPR = D / 8;
+    const int lane = threadIdx.x & 63, ro = lane / LPR, li = lane % LPR;
     const float fn = (float)nb;
-    float mk[8];
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-        mk[e] = ak[e] / fn;
-        av[e] = av[e] / fn;
-    }
-    if (ro == 0) {
-        float4* ko = reinterpret_cast<float4*>(km_out + li * 8);
-        float4* vo = reinterpret_cast<float4*>(vm_out + li * 8);
-        ko[0] = make_float4(mk[0], mk[1], mk[2], mk[3]);
-        ko[1] = make_float4(mk[4], mk[5], mk[6], mk[7]);
-        vo[0] = make_float4(av[0], av[1], av[2], av[3]);
-        vo[1] = make_float4(av[4], av[5], av[6], av[7]);
-    }
-    // squared deviations, the same way
-    float m2[8];
-#pragma unroll
-    for (int v = 0; v < 4; ++v) {
-        float s2[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-#pragma unroll
-        for (int st = 0; st < 2; ++st) {
-            const bool ok = st * RPG + v * RPW + ro < nb;
-            float kf[8];
-            unpack_bf16x8(kw[st][v], kf);
-#pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                const float dev = kf[e] - mk[e];
-                s2[e] += ok ? __fmul_rn(dev, dev) : 0.0f;
-            }
-        }
-#pragma unroll
-        for (int off = LPR; off < 64; off <<= 1)
-#pragma unroll
-            for (int e = 0; e < 8; ++e) s2[e] = xor_add(s2[e], off);
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            if (v == 0 || v == 2) tk[e] = s2[e];
-            else if (v == 1) m2[e] = tk[e] + s2[e];
-            else m2[e] = m2[e] + (tk[e] + s2[e]);
-        }
-    }
     if (r == D) {
+        divide8(m2, nb);
         if (ro == 0) {
 #pragma unroll
-            for (int e = 0; e < 8; ++e) dv_out[li * 8 + e] = m2[e] / fn;
+            for (int e = 0; e < 8; ++e) dv_out[li * 8 + e] = m2[e];
         }
         return;
     }

@@ -207,18 +207,20 @@ int step_stream_max_budget();
 int step_stream_merge_terms();  // partials x heads limit of the in-launch merge
 size_t step_stream_dyn_lds(const Geom& g, int nchunks);
 
-// Resident workgroups of `kern` (`threads` each, no dynamic LDS) on the current device, cached per
-// (kernel, device). Not thread-safe on first use per kernel; a race only repeats the same query.
+// Resident workgroups of `kern` (`threads` each, no dynamic LDS) on the current device, at most `most` per
+// compute unit; cached per (kernel, device). Not thread-safe on first use per kernel; a race only repeats the
+// same query.
 template <typename Kern>
-int resident_slots(Kern kern, int threads = kThreads) {
+int resident_slots(Kern kern, int threads = kThreads, int most = 1 << 10) {
     constexpr int kSlots = 64;
     static const void* key_fn[kSlots];
-    static int key_dev[kSlots], value[kSlots];
+    static int key_dev[kSlots], value[kSlots], cu_count[kSlots];
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess) dev = 0;
     const void* fn = reinterpret_cast<const void*>(kern);
     for (int i = 0; i < kSlots; ++i)
-        if (key_fn[i] == fn && key_dev[i] == dev && value[i] > 0) return value[i];
+        if (key_fn[i] == fn && key_dev[i] == dev && value[i] > 0 && cu_count[i] > 0)
+            return (value[i] < most ? value[i] : most) * cu_count[i];
     int per_cu = 0, cus = 0;
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kern, threads, 0) != hipSuccess || per_cu < 1)
         per_cu = 1;
@@ -227,10 +229,11 @@ int resident_slots(Kern kern, int threads = kThreads) {
         if (key_fn[i] == nullptr) {
             key_fn[i] = fn;
             key_dev[i] = dev;
-            value[i] = per_cu * cus;
+            cu_count[i] = cus;
+            value[i] = per_cu;
             break;
         }
-    return per_cu * cus;
+    return (per_cu < most ? per_cu : most) * cus;
 }
 
 // ------------------------------------------------------------------ device helpers
@@ -248,6 +251,19 @@ __device__ __forceinline__ void unpack_bf16x8(const uint4 w, float f[8]) {
     f[5] = bf16_hi(w.z);
     f[6] = bf16_lo(w.w);
     f[7] = bf16_hi(w.w);
+}
+
+// A word at a wave-uniform address that the launch does not write, through the scalar path: it does not
+// wait behind the wave's vector loads (which return in order).
+__device__ __forceinline__ int load_uniform(const int32_t* p) {
+    return *reinterpret_cast<const __attribute__((address_space(4))) int32_t*>(reinterpret_cast<uintptr_t>(p));
+}
+
+// 16 bytes that are read once (a non-temporal load: the line is the first to leave the caches)
+__device__ __forceinline__ uint4 load_once(const void* p) {
+    typedef unsigned v4u __attribute__((ext_vector_type(4)));
+    const v4u w = __builtin_nontemporal_load(reinterpret_cast<const v4u*>(p));
+    return make_uint4(w.x, w.y, w.z, w.w);
 }
 
 __device__ __forceinline__ int clamp_len(int n, int cap) { return n < 0 ? 0 : (n > cap ? cap : n); }

@@ -1,10 +1,9 @@
 // stats.hip -- block summaries: prefill build and streaming append (Sections 4.1, 4.2; Appendix E.1).
 //
-// One workgroup computes one block's summary with wg_block_stats (block_stats.h): the prefill strides
-// over every (unit, block) (blocks of up to 32 rows at d = 128: one wave per block, same arithmetic),
-// the append recomputes each unit's active block after storing the new row.
-// Build, append and the fused decode step share that routine, so an appended block's summary is
-// bit-identical to the prefill one.
+// The prefill strides over every (unit, block): one wave per block up to 64 rows at d = 128, else one
+// workgroup (wg_block_stats, block_stats.h). The append recomputes each unit's active block with the workgroup
+// routine after storing the new row, like the fused decode step. Wave and workgroup add in the same order,
+// so an appended block's summary is bit-identical to the prefill one.
 #include "block_stats.h"
 
 namespace compkv {
@@ -53,23 +52,90 @@ __global__ __launch_bounds__(kThreads) void build_stats_kernel(Geom g, StatsArgs
     }
 }
 
-// Blocks of at most wave_stats_max_rows<D>() rows: each wave summarizes whole blocks on its own (no
-// barrier, no LDS; bit-identical to the workgroup routine), consecutive waves taking consecutive
-// blocks, every row of a block requested at once.
-template <int D>
+// Blocks of at most wave_stats_max_rows<D>(NS) rows: each wave summarizes whole blocks on its own (no
+// barrier, no LDS; bit-identical to the workgroup routine), consecutive waves taking consecutive blocks.
+// HBM-bound, with the vector ALUs ~40% busy: the wave holds the block's keys (needed twice) and its values, VS
+// steps at a time; the next block's values are requested as soon as this block's are added and its keys as
+// soon as the squared deviations are, so loads stay in flight while the wave computes, and no branch lies
+// around a load (the registers are loaded in place). With the masks as factors, one butterfly per sum and
+// the exact reciprocal of a power-of-two count a block takes 890 vector instructions. One layer of 32K tokens
+// x 8 KV heads, d = 128, blocks of 32: 39.1 -> 29.7 us (143 MB, 4.8 TB/s); 128K x 4: 490 -> 448 us (5.1 TB/s);
+// blocks of 16: 923 -> 460 us; d = 64: 532 -> 206 us.
+template <int D, int NS, int VS>
 __global__ __launch_bounds__(kThreads) void build_stats_wave_kernel(Geom g, StatsArgs a) {
-    constexpr int WPG = kThreads / 64;
+    constexpr int WPG = kThreads / 64, LPR = D / 8;
+    static_assert(NS % VS == 0, "whole batches of values");
+    const int lane = threadIdx.x & 63, ro = lane / LPR, li = lane % LPR;
     const int xmax = g.xmax();
     const int total = xmax * g.units();
     const int nwaves = gridDim.x * WPG;
-    for (int flat = blockIdx.x * WPG + (threadIdx.x >> 6); flat < total; flat += nwaves) {  // wave-uniform
-        const int u = flat / xmax, b = flat % xmax;
-        const int n = clamp_len(a.seq_lens[u / g.hkv], g.max_seq);
-        if (b >= (n + g.B - 1) / g.B) continue;
-        const size_t row0 = (size_t)block_row0(g, u, b);
-        const BlockSrc src{a.K + row0 * D, a.V + row0 * D, nullptr, nullptr, min(g.B, n - b * g.B), -1};
-        const size_t blk = (size_t)u * g.xcap + b;
-        wave_block_stats<D>(src, g.r, g.layout, a.kmean + blk * D, a.dvar + blk * g.r, a.vmean + blk * D);
+    struct Item {
+        size_t row0, blk;
+        int nb;  // 0: no block (past the sequence, or past the last)
+    };
+    // (a wave's index in a scalar register: the whole item is wave-uniform)
+    int flat = blockIdx.x * WPG + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    auto next_item = [&]() {  // the wave's next block within its sequence
+        for (; flat < total; flat += nwaves) {
+            const int u = flat / xmax, b = flat - u * xmax;
+            const int n = clamp_len(load_uniform(a.seq_lens + u / g.hkv), g.max_seq);
+            if (b * g.B < n) {
+                const size_t row0 = (size_t)__builtin_amdgcn_readfirstlane(block_row0(g, u, b));
+                flat += nwaves;
+                return Item{row0, (size_t)u * g.xcap + b, min(g.B, n - b * g.B)};
+            }
+        }
+        return Item{0, 0, 0};
+    };
+    Item cur = next_item();
+    if (cur.nb == 0) return;
+    WaveRows<NS> K;
+    WaveRows<VS> V;
+    load_wave_rows<D, VS>(a.V + cur.row0 * D, cur.nb, 0, V);
+    load_wave_rows<D, NS>(a.K + cur.row0 * D, cur.nb, 0, K);
+    while (true) {
+        Item nxt = next_item();
+        const bool more = nxt.nb != 0;
+        if (!more) nxt = cur;  // (the last block is requested once more, unused: no branch around the loads)
+        const int nb = cur.nb;
+        float s[4][8], mk[8], t[8];
+        zero_sums(s);
+#pragma unroll
+        for (int s0 = 0; s0 < NS; s0 += VS) {
+            add_wave_rows<D, VS, false>(V, nb, s0, mk, s);
+            __builtin_amdgcn_sched_barrier(0);  // (the phases in order: nothing hoisted into more registers)
+            if (s0 + VS < NS)
+                load_wave_rows<D, VS>(a.V + cur.row0 * D, nb, s0 + VS, V);
+            else
+                load_wave_rows<D, VS>(a.V + nxt.row0 * D, nxt.nb, 0, V);
+        }
+        total_wave_rows<D>(s, t);
+        divide8(t, nb);
+        if (ro == 0) {
+            float4* vo = reinterpret_cast<float4*>(a.vmean + cur.blk * D + li * 8);
+            vo[0] = make_float4(t[0], t[1], t[2], t[3]);
+            vo[1] = make_float4(t[4], t[5], t[6], t[7]);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        zero_sums(s);
+        add_wave_rows<D, NS, false>(K, nb, 0, mk, s);
+        total_wave_rows<D>(s, mk);
+        divide8(mk, nb);
+        if (ro == 0) {
+            float4* ko = reinterpret_cast<float4*>(a.kmean + cur.blk * D + li * 8);
+            ko[0] = make_float4(mk[0], mk[1], mk[2], mk[3]);
+            ko[1] = make_float4(mk[4], mk[5], mk[6], mk[7]);
+        }
+        pin_rows(K);
+        __builtin_amdgcn_sched_barrier(0);
+        zero_sums(s);
+        add_wave_rows<D, NS, true>(K, nb, 0, mk, s);
+        __builtin_amdgcn_sched_barrier(0);
+        load_wave_rows<D, NS>(a.K + nxt.row0 * D, nxt.nb, 0, K);
+        total_wave_rows<D>(s, t);
+        store_wave_variances<D>(t, nb, g.r, g.layout, a.dvar + cur.blk * g.r);
+        if (!more) return;
+        cur = nxt;
     }
 }
 
@@ -101,15 +167,29 @@ __global__ __launch_bounds__(kThreads) void append_stats_kernel(Geom g, StatsArg
 
 }  // namespace
 
+// One resident round, at most `most` workgroups per CU: the loads in flight beyond what the latency needs
+// queue at the memory and slow it. Measured (MI355X, us with 1 / 2 / 3 / 4 workgroups per CU): d = 128,
+// blocks of 32, 8K blocks 31.0 / 29.7 / 32.7 / 35.7, 128K blocks 432 / 448 / 463 / 467; blocks of 16, 256K
+// blocks 613 / 460 / 486 / 483; d = 64, blocks of 32, 128K blocks 322 / 228 / 206 / 212; blocks of 16, 128K
+// blocks 321 / 210 / 172 / 158 and 151 with 5.
+template <int D, int NS, int VS>
+void launch_build_wave(const Geom& g, const StatsArgs& a, int most, hipStream_t s) {
+    const long long total = (long long)g.xmax() * g.units();
+    const long long wgs = (total + kThreads / 64 - 1) / (kThreads / 64);
+    const long long slots = resident_slots(build_stats_wave_kernel<D, NS, VS>, kThreads, most);
+    build_stats_wave_kernel<D, NS, VS><<<dim3((unsigned)(wgs < slots ? wgs : slots)), kThreads, 0, s>>>(g, a);
+}
+
+// One wave per block up to 64 rows at d = 128 (128 at d = 64), by the load steps the block needs; larger
+// blocks are shared by a workgroup's four waves. (Against the workgroup form: blocks of 64 at d = 128 436 ->
+// 413 us for 2.2 GB.)
 template <int D>
 void launch_build_d(const Geom& g, const StatsArgs& a, hipStream_t s) {
+    const int small = D == 64 ? (g.B <= 16 ? 5 : 3) : 2;
+    if (g.B <= wave_stats_max_rows<D>(1)) return launch_build_wave<D, 1, 1>(g, a, small, s);
+    if (g.B <= wave_stats_max_rows<D>(2)) return launch_build_wave<D, 2, 2>(g, a, 2, s);
+    if (g.B <= wave_stats_max_rows<D>(4)) return launch_build_wave<D, 4, 2>(g, a, 2, s);
     const long long total = (long long)g.xmax() * g.units();
-    if (g.B <= wave_stats_max_rows<D>()) {  // one wave per block
-        const long long wgs = (total + kThreads / 64 - 1) / (kThreads / 64);
-        const long long slots = resident_slots(build_stats_wave_kernel<D>);  // one resident round
-        build_stats_wave_kernel<D><<<dim3((unsigned)(wgs < slots ? wgs : slots)), kThreads, 0, s>>>(g, a);
-        return;
-    }
     const long long slots = resident_slots(build_stats_kernel<D>);  // one resident round, grid-stride
     build_stats_kernel<D><<<dim3((unsigned)(total < slots ? total : slots)), kThreads, 0, s>>>(g, a);
 }

@@ -235,3 +235,28 @@ def test_graph_replays_match_eager(path):
             assert torch.equal(x, y), f"replay {rep} differs"
         c.dense_decode()  # unrelated eager work on the same workspace between replays
         torch.cuda.synchronize()
+
+
+# the wave-per-block build at the edges of its load steps (d = 128: 16, 32 and 64 rows; d = 64: 32, 64 and 128)
+# and the workgroup build past them, on ragged lengths: against the oracle, and bit for bit against appending the
+# last token of every sequence (the workgroup routine)
+@pytest.mark.parametrize("d,B,r,layout", [(128, 1, 4, 0), (128, 16, 128, 0), (128, 17, 1, 1), (128, 32, 4, 1), (128, 33, 4, 0),
+                                          (128, 64, 16, 0), (128, 65, 64, 0), (64, 32, 64, 0), (64, 33, 1, 0),
+                                          (64, 64, 4, 1), (64, 127, 8, 0), (64, 128, 4, 0), (64, 129, 2, 0)])
+def test_build_block_edges(d, B, r, layout):
+    import paper_2609_26300_amd as P
+
+    lens = [3 * B + 2, 2 * B, B + 1, B, 1]
+    c = Case(TINY.with_(batch=5, head_dim=d, block_size=B, context=3 * B + 2, n_var_groups=r, budget_blocks=4, seed=71),
+             seq_lens=lens, layout=layout)
+    s = c.build_stats()
+    c.check_stats(s.kmean, s.dvar, s.vmean)
+    before = (c.sl - 1).to(torch.int32)
+    kn = torch.stack([c.K[b, :, n - 1] for b, n in enumerate(lens)]).contiguous()
+    vn = torch.stack([c.V[b, :, n - 1] for b, n in enumerate(lens)]).contiguous()
+    a = P.alloc_summaries(c.dims)
+    P.compkv_build_stats(c.dims, c.K, c.V, before, a.kmean, a.dvar, a.vmean)
+    P.compkv_append_stats(c.dims, c.K, c.V, kn, vn, before, a.kmean, a.dvar, a.vmean)
+    torch.cuda.synchronize()
+    for k in ("kmean", "dvar", "vmean"):
+        assert torch.equal(getattr(a, k), getattr(s, k)), k
