@@ -12,7 +12,7 @@ CSRC = os.path.join(PKG, "csrc")
 INCLUDE = os.path.join(ROOT, "include")
 BUILD = os.path.join(ROOT, "_build")
 LIB = os.path.join(PKG, "libcompkv.so")
-SOURCES = ["api.hip", "stats.hip", "select.hip", "decode.hip", "step.hip"]
+SOURCES = ["api.hip", "stats.hip", "select.hip", "fused.hip", "decode.hip", "step.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 ARCH = "gfx950"
 FLAGS = [

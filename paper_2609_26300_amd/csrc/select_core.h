@@ -1,5 +1,5 @@
-// select_core.h -- pieces of the scoring, selection and fused decode kernels shared by select.hip and
-// step.hip (private to libcompkv): query preparation, score kinds, the Top-K selection of one unit
+// select_core.h -- pieces of the scoring, selection and fused decode kernels shared by select.hip,
+// fused.hip and step.hip (private to libcompkv): query preparation, score kinds, the Top-K selection of one unit
 // from chunk partials, the compensation stream of mean values and the in-launch merge of partials.
 #pragma once
 

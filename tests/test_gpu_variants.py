@@ -14,7 +14,7 @@ import torch
 
 import oracle
 import paper_2609_26300_amd as P
-from gpu_case import CASES, PATHS, TOL, check_selection, make_case, rel_err
+from gpu_case import CASES, PATHS, TINY, TOL, Case, check_selection, make_case, rel_err
 from workloads import offset_blocks
 
 pytestmark = pytest.mark.gpu
@@ -113,3 +113,21 @@ def test_offset_blocks_mass_vs_compkv_on_gpu(path):
         offs = [len(offset_blocks(c.w, 0, b, h)) for b, h in c.units()]
     assert counts[P.COMPKV_SCORE_MASS] == offs
     assert counts[P.COMPKV_SCORE_COMPKV] == [0] * len(offs)
+
+
+# more than eight variance groups in the chunk scoring (one, two and four slots of 32 blocks per chunk): against
+# the oracle, and bit for bit against the streaming shape's scoring, which loads the variances one by one
+@pytest.mark.parametrize("d,r,batch,context,B", [(128, 16, 1, 1001, 16), (128, 128, 2, 300, 1), (64, 32, 1, 700, 8),
+                                                 (64, 64, 64, 530, 1), (128, 32, 64, 1000, 1)])
+def test_wide_variances_chunks(d, r, batch, context, B):
+    c = Case(TINY.with_(batch=batch, head_dim=d, block_size=B, context=context, n_var_groups=r, budget_blocks=8, seed=72),
+             seq_lens=[max(1, context - 13 * i) for i in range(batch)])
+    c.select_path = P.COMPKV_SELECT_CHUNKED
+    c.build_stats()
+    c.score_select()
+    c.select_path = P.COMPKV_SELECT_STREAM
+    got = c.decode_step()
+    torch.cuda.synchronize()
+    for k in ("sel", "n_sel", "blk_logit", "scores"):
+        assert torch.equal(got[k], getattr(c, k)), k
+    c.check_step(got["sel"], got["n_sel"], got["out"], got["lse"])
