@@ -11,6 +11,7 @@ import torch
 
 _PKG = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_PKG, "libcompkv.so")
+HOST_PATH = os.path.join(_PKG, "_host.so")
 HEADER_PATH = os.path.join(os.path.dirname(_PKG), "include", "compkv.h")
 
 COMPKV_GROUPS_ROTATE_HALF = 0
@@ -131,6 +132,73 @@ def library():
     return _lib
 
 
+# The usual call path: _host (csrc/host.cpp) checks the tensors and enters the library natively. Its kinds:
+_BUILD, _APPEND, _SCORE, _SPARSE, _DENSE, _STEP, _STEP_NOALLOC = range(7)
+_ENTRIES = ("compkv_build_stats", "compkv_append_stats", "compkv_score_select", "compkv_sparse_decode",
+            "compkv_dense_decode", "compkv_decode_step", "compkv_decode_step_noalloc")
+_host_call = None
+_entries: tuple = (None, ())  # the library the addresses belong to, the functions' addresses
+_specs: dict = {}  # what each argument has to be, by the call's kind, the dims' values and the budget
+_MOST_SPECS = 256
+
+
+def _load_host():
+    global _host_call
+    if not os.path.exists(HOST_PATH):
+        raise CompkvError(f"{HOST_PATH} is not built; run __graft_entry__.build() or "
+                          "python -m paper_2609_26300_amd.build")
+    import importlib.machinery
+    import importlib.util
+
+    loader = importlib.machinery.ExtensionFileLoader("_host", HOST_PATH)
+    mod = importlib.util.module_from_spec(importlib.util.spec_from_loader("_host", loader))
+    loader.exec_module(mod)
+    _host_call = mod.call
+
+
+def _call(kind, dims, K, args):
+    """Status of the call with `args` (after dims), or None where the checks in Python have to decide."""
+    global _entries
+    lib = library()
+    if _host_call is None:
+        _load_host()
+    if _entries[0] is not lib:
+        _entries = (lib, tuple(ctypes.cast(getattr(lib, f), _vp).value for f in _ENTRIES))
+    key = (kind, bytes(dims), K)
+    spec = _specs.get(key)
+    if spec is None:
+        if len(_specs) >= _MOST_SPECS:
+            _specs.clear()
+        spec = _specs[key] = _call_spec(kind, dims, K)
+    return _host_call(kind, _entries[1][kind], (ctypes.addressof(dims), *args), spec)
+
+
+def _call_spec(kind, d, K):
+    bf, f32, i32 = torch.bfloat16, torch.float32, torch.int32
+    cache, summ, dvar, q = _shapes(d)
+    units = (d.batch, d.n_kv_heads)
+    new = (*units, d.head_dim)
+    KV, SUM, DV, Q = (bf, cache, False), (f32, summ, False), (f32, dvar, False), (bf, q, False)
+    SEQ, NEW = (i32, (d.batch,), False), (bf, new, False)
+    SEL, NSEL = (i32, (*units, K), False), (i32, units, False)
+    blk, scores = (*units, d.group, d.xcap), (*units, d.xcap)
+    OUT, LSE = (f32, q, False), (f32, q[:2], True)
+    if kind == _BUILD:
+        return (None, KV, KV, SEQ, SUM, DV, SUM, None)
+    if kind == _APPEND:
+        return (None, KV, KV, NEW, NEW, SEQ, SUM, DV, SUM, None)
+    if kind == _SCORE:
+        return (None, None, Q, SUM, DV, SEQ, SEL, NSEL, (f32, blk, True), (f32, scores, True), True, None)
+    if kind == _SPARSE:
+        return (None, None, Q, KV, KV, (f32, summ, True), (f32, summ, True), (f32, blk, True), SEQ, SEL, NSEL, None, OUT,
+                LSE, True, None)
+    if kind == _DENSE:
+        return (None, None, Q, KV, KV, SEQ, OUT, LSE, True, None)
+    step = (None, None, Q, KV, KV, (bf, new, True), (bf, new, True), SEQ, SUM, DV, SUM, SEL, NSEL, (f32, blk, False),
+            (f32, scores, True), OUT, LSE)
+    return (*step, True, None) if kind == _STEP else (*step, None)
+
+
 def exported_symbols() -> list[str]:
     """Function names declared in include/compkv.h."""
     text = open(HEADER_PATH).read()
@@ -191,6 +259,15 @@ def _stream(stream):
     return stream.cuda_stream if isinstance(stream, torch.cuda.Stream) else stream
 
 
+def _raw_stream(stream):
+    """The stream as an integer for the native call path, or None where the checks in Python go first."""
+    if stream is None:
+        if not torch.cuda.is_initialized():
+            return None
+        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())  # (the current stream's handle)
+    return _stream(stream)
+
+
 def _ws(workspace):
     if workspace is None or workspace.device.type != "cuda" or not workspace.is_contiguous():
         raise CompkvError("workspace must be a contiguous CUDA tensor")
@@ -242,6 +319,9 @@ def _shapes(d: CompkvDims):
 
 
 def compkv_build_stats(dims, k_cache, v_cache, seq_lens, kmean, dvar, vmean, stream=None):
+    st = _call(_BUILD, dims, 0, (k_cache, v_cache, seq_lens, kmean, dvar, vmean, _raw_stream(stream)))
+    if st is not None:
+        return _check(st, "compkv_build_stats")
     cache, summ, dv, _ = _shapes(dims)
     bf, f32 = torch.bfloat16, torch.float32
     st = library().compkv_build_stats(
@@ -252,6 +332,9 @@ def compkv_build_stats(dims, k_cache, v_cache, seq_lens, kmean, dvar, vmean, str
 
 
 def compkv_append_stats(dims, k_cache, v_cache, k_new, v_new, seq_lens, kmean, dvar, vmean, stream=None):
+    st = _call(_APPEND, dims, 0, (k_cache, v_cache, k_new, v_new, seq_lens, kmean, dvar, vmean, _raw_stream(stream)))
+    if st is not None:
+        return _check(st, "compkv_append_stats")
     cache, summ, dv, _ = _shapes(dims)
     bf, f32 = torch.bfloat16, torch.float32
     new = (dims.batch, dims.n_kv_heads, dims.head_dim)
@@ -265,6 +348,10 @@ def compkv_append_stats(dims, k_cache, v_cache, k_new, v_new, seq_lens, kmean, d
 
 def compkv_score_select(dims, params: CompkvSelectParams, q, kmean, dvar, seq_lens, sel, n_sel, blk_logit,
                         scores, workspace, stream=None):
+    st = _call(_SCORE, dims, params.budget_blocks, (ctypes.addressof(params), q, kmean, dvar, seq_lens, sel, n_sel,
+                                                    blk_logit, scores, workspace, _raw_stream(stream)))
+    if st is not None:
+        return _check(st, "compkv_score_select")
     _, summ, dv, qs = _shapes(dims)
     f32, i32 = torch.float32, torch.int32
     units = (dims.batch, dims.n_kv_heads)
@@ -283,6 +370,12 @@ def compkv_sparse_decode(dims, scale, q, k_cache, v_cache, vmean, blk_logit, seq
                          lse=None, workspace=None, stream=None, kmean=None):
     """Compensated sparse decode; vmean = blk_logit = None gives the Drop decode. With blk_logit None
     and vmean given, the block-mean logits are recomputed from kmean."""
+    if sel is not None and sel.dim() == 3:
+        K = int(sel.shape[2])
+        st = _call(_SPARSE, dims, K, (float(scale), q, k_cache, v_cache, kmean, vmean, blk_logit, seq_lens, sel, n_sel, K,
+                                      out, lse, workspace, _raw_stream(stream)))
+        if st is not None:
+            return _check(st, "compkv_sparse_decode")
     cache, summ, _, qs = _shapes(dims)
     bf, f32, i32 = torch.bfloat16, torch.float32, torch.int32
     units = (dims.batch, dims.n_kv_heads)
@@ -301,6 +394,9 @@ def compkv_sparse_decode(dims, scale, q, k_cache, v_cache, vmean, blk_logit, seq
 
 
 def compkv_dense_decode(dims, scale, q, k_cache, v_cache, seq_lens, out, lse=None, workspace=None, stream=None):
+    st = _call(_DENSE, dims, 0, (float(scale), q, k_cache, v_cache, seq_lens, out, lse, workspace, _raw_stream(stream)))
+    if st is not None:
+        return _check(st, "compkv_dense_decode")
     cache, _, _, qs = _shapes(dims)
     bf, f32 = torch.bfloat16, torch.float32
     ws, ws_bytes = _ws(workspace)
@@ -315,6 +411,12 @@ def compkv_dense_decode(dims, scale, q, k_cache, v_cache, seq_lens, out, lse=Non
 def compkv_decode_step(dims, params: CompkvSelectParams, q, k_cache, v_cache, k_new, v_new, seq_lens, kmean,
                        dvar, vmean, sel, n_sel, blk_logit, scores, out, lse=None, workspace=None, stream=None):
     """One fused decode step; seq_lens are the lengths after the new token (k_new/v_new may be None)."""
+    if (k_new is None) == (v_new is None):
+        st = _call(_STEP, dims, params.budget_blocks, (
+            ctypes.addressof(params), q, k_cache, v_cache, k_new, v_new, seq_lens, kmean, dvar, vmean, sel, n_sel,
+            blk_logit, scores, out, lse, workspace, _raw_stream(stream)))
+        if st is not None:
+            return _check(st, "compkv_decode_step")
     cache, summ, dv, qs = _shapes(dims)
     bf, f32, i32 = torch.bfloat16, torch.float32, torch.int32
     units = (dims.batch, dims.n_kv_heads)
@@ -338,6 +440,12 @@ def compkv_decode_step_noalloc(dims, params: CompkvSelectParams, q, k_cache, v_c
                                kmean, dvar, vmean, sel, n_sel, blk_logit, scores, out, lse=None, stream=None):
     """compkv_decode_step without a workspace: the library's fixed per-GPU scratch is used instead
     (nothing is allocated; overlapping calls on one GPU race)."""
+    if (k_new is None) == (v_new is None):
+        st = _call(_STEP_NOALLOC, dims, params.budget_blocks, (
+            ctypes.addressof(params), q, k_cache, v_cache, k_new, v_new, seq_lens, kmean, dvar, vmean, sel, n_sel,
+            blk_logit, scores, out, lse, _raw_stream(stream)))
+        if st is not None:
+            return _check(st, "compkv_decode_step_noalloc")
     cache, summ, dv, qs = _shapes(dims)
     bf, f32, i32 = torch.bfloat16, torch.float32, torch.int32
     units = (dims.batch, dims.n_kv_heads)

@@ -38,6 +38,25 @@ def _run(cmd, verbose):
     return res
 
 
+HOST_LIB = os.path.join(PKG, "_host.so")
+
+
+def build_host(verbose: bool = False) -> str:
+    """_host.so: the binding's call path in native code (csrc/host.cpp, host code only)."""
+    import sysconfig
+
+    from torch.utils import cpp_extension
+
+    tmp = HOST_LIB + f".tmp{os.getpid()}"
+    dirs = [d for d in cpp_extension.include_paths() + [sysconfig.get_paths()["include"], INCLUDE]]
+    libs = cpp_extension.library_paths()
+    _run(["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", *(f"-I{d}" for d in dirs),
+          os.path.join(CSRC, "host.cpp"), "-o", tmp, *(f"-L{d}" for d in libs), "-ltorch_python", "-ltorch",
+          "-ltorch_cpu", "-lc10"], verbose)
+    os.replace(tmp, HOST_LIB)
+    return HOST_LIB
+
+
 TRACE_LIB = os.path.join(PKG, "libcompkv_trace.so")
 
 
@@ -59,6 +78,8 @@ def build(verbose: bool = False, jobs: int = 4, trace: bool = False) -> str:
     tmp = lib + f".tmp{os.getpid()}"
     _run([HIPCC, f"--offload-arch={ARCH}", "-shared", "-fPIC", "-o", tmp, *objs], verbose)
     os.replace(tmp, lib)
+    if not trace:
+        build_host(verbose)
     return lib
 
 

@@ -75,6 +75,18 @@ int check_dims(const compkv_dims* dm, Geom* g) {
 
 // ---------------------------------------------------------------- launch shapes
 
+// compute units of the current device (`unknown` where it cannot be asked); each thread keeps the last answer
+int device_cus(int unknown) {
+    static thread_local int known_dev = -1, known_cus = 0;
+    int dev = 0, cus = 0;
+    if (hipGetDevice(&dev) != hipSuccess) return unknown;
+    if (dev == known_dev) return known_cus;
+    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return unknown;
+    known_dev = dev;
+    known_cus = cus;
+    return cus;
+}
+
 struct ScoreShape {
     int bpc, nchunks;
 };
@@ -226,9 +238,7 @@ bool one_group_path(const Geom& g, int path, int* st) {
 SxShape sx_shape(const Geom& g, int nchunks, int K) {
     const int xmax = g.xmax();
     const int keff = std::max(1, std::min(K, xmax));
-    int cus = 0, dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
-        cus = 0;
+    const int cus = device_cus(0);
     // one resident round of workgroups (two per CU): up to half of a unit's share goes to compensation
     // workgroups (of at least 128 and at most select_exact_max_cb() blocks each: few partials to merge)
     // and the rest to exact items, the smallest of at least 64 tokens that fit it (an item of more
@@ -286,9 +296,7 @@ SxShape sx_shape(const Geom& g, int nchunks, int K) {
 StreamShape stream_shape(const Geom& g, int K, bool mean) {
     const int xmax = g.xmax();
     const int keff = std::max(1, std::min(K, xmax));
-    int cus = 0, dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
-        cus = 256;
+    const int cus = device_cus(256);
     const int units = g.units();
     int n_comp = 0, cb = 0;
     if (mean) {

@@ -298,17 +298,29 @@ int select_exact_max_cb() { return kStepCbMax; }
 int select_exact_merge_terms() { return kMergeMaxTerms; }
 
 // Resident workgroups of the one-selector fused launch on the current device with `dyn` bytes of
-// dynamic LDS each.
+// dynamic LDS each. The answer depends on nothing else, and every step asks it several times: each thread keeps
+// the last few (a query takes about a microsecond).
 template <int D, int G>
 int sx_slots(size_t dyn, int threads) {
+    struct Known {
+        int dev, threads, slots;
+        size_t dyn;
+    };
+    constexpr int kKnown = 8;
+    static thread_local Known known[kKnown];
+    static thread_local int count = 0;
     int per_cu = 0, cus = 0, dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess ||
-        (threads == kSxThreads
+    if (hipGetDevice(&dev) != hipSuccess) return 0;
+    for (int i = 0; i < (count < kKnown ? count : kKnown); ++i)
+        if (known[i].dev == dev && known[i].threads == threads && known[i].dyn == dyn) return known[i].slots;
+    if ((threads == kSxThreads
              ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, select_work_kernel<D, G, 1024, 8>, 1024, dyn)
              : hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, select_work_kernel<D, G, 512, 16>, 512, dyn)) !=
             hipSuccess ||
         hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
         return 0;
+    known[count % kKnown] = {dev, threads, per_cu * cus, dyn};
+    count = count + 1 < (1 << 30) ? count + 1 : kKnown;
     return per_cu * cus;
 }
 template <int D>
