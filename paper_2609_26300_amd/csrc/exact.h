@@ -34,9 +34,6 @@ constexpr int kMaxEb = 128;  // selected blocks per exact item, upper bound
 template <int D, int G, int NW>
 struct ExactLds {
     float m[NW][G], l[NW][G];
-    float f[NW][G];  // each wave's rescale factor exp(m_w - M) per head
-    float fx[G];     // the same for an absorbed partial (finish_exact's xm, xl, xacc)
-    float M[G], L[G];
     alignas(16) float acc[NW][G][D];
     float zb[G][kMaxEb];  // fused step: the block logits of the item's selected blocks
 };
@@ -265,8 +262,8 @@ __device__ void exact_tokens(const TokenMap& tm, const uint16_t* __restrict__ Ku
     l += __shfl_xor(l, 32);
 }
 
-// Combine the NW waves' exact states in LDS and write the item's partial: the per-head maximum M
-// over the waves and each wave's factor exp(m_w - M) first, then every coordinate as a plain sum of
+// Combine the NW waves' exact states in LDS and write the item's partial: each wave forms its head's maximum
+// M over the waves and each wave's factor exp(m_w - M), then every coordinate as a plain sum of
 // the waves' scaled accumulators in wave order. kCoherent: the partial is stored with device-coherent
 // stores (merged by another workgroup of the same launch). With xm non-null, one more partial in LDS
 // (per head: max xm[g], sum xl[g], weighted sums xacc[g * xstride + i]) is absorbed after the waves.
@@ -292,45 +289,44 @@ __device__ void finish_exact(float m, float l, const v4f32 (&acc)[D / 16], Exact
         }
     }
     __syncthreads();
-    if (tid < G) {
-        const int g = tid;
-        float M = -INFINITY;
-#pragma unroll
-        for (int w = 0; w < NW; ++w) M = fmaxf(M, sh.m[w][g]);
-        if (xm) M = fmaxf(M, xm[g]);
-        float L = 0.0f;
-#pragma unroll
-        for (int w = 0; w < NW; ++w) {
-            const float fw = sh.m[w][g] == -INFINITY ? 0.0f : __expf(sh.m[w][g] - M);
-            sh.f[w][g] = fw;
-            L += fw * sh.l[w][g];
-        }
-        if (xm) {
-            const float fx = xm[g] == -INFINITY ? 0.0f : __expf(xm[g] - M);
-            sh.fx[g] = fx;
-            L += fx * xl[g];
-        }
-        sh.M[g] = M;
-        sh.L[g] = L;
-    }
-    __syncthreads();
+    static_assert(NW == 8 || NW == 16, "a row of 16 lanes holds the waves' states");
+    static_assert(D % 64 == 0, "the 64 coordinates of a wave belong to one head");
     for (int idx = tid; idx < G * D; idx += 64 * NW) {
-        const int g = idx / D, i = idx % D;
+        const int g = __builtin_amdgcn_readfirstlane(idx / D), i = idx % D;
+        // every wave forms its head's maximum, sum and factors from the waves' states (lane w of each row of
+        // 16: wave w), without another barrier
+        const float mw = sh.m[lane & (NW - 1)][g], lw = (lane & 15) < NW ? sh.l[lane & (NW - 1)][g] : 0.0f;
+        float M = mw;
+        M = fmaxf(M, dpp_f<0xB1>(M));
+        M = fmaxf(M, dpp_f<0x4E>(M));
+        M = fmaxf(M, dpp_f<0x124>(M));
+        M = fmaxf(M, dpp_f<0x128>(M));
+        if (xm) M = fmaxf(M, xm[g]);
+        const float f = mw == -INFINITY ? 0.0f : __expf(mw - M);
+        float L = f * lw;
+        L += dpp_f<0xB1>(L);
+        L += dpp_f<0x4E>(L);
+        L += dpp_f<0x124>(L);
+        L += dpp_f<0x128>(L);
         float aa = 0.0f;
 #pragma unroll
-        for (int w = 0; w < NW; ++w) aa += sh.f[w][g] * sh.acc[w][g][i];
-        if (xm) aa += sh.fx[g] * xacc[(size_t)g * xstride + i];
+        for (int w = 0; w < NW; ++w) aa += readlane_f(f, w) * sh.acc[w][g][i];
+        if (xm) {
+            const float fx = xm[g] == -INFINITY ? 0.0f : __expf(xm[g] - M);
+            L += fx * xl[g];
+            aa += fx * xacc[(size_t)g * xstride + i];
+        }
         float* p = part + (size_t)g * (D + 2);
         if constexpr (kCoherent) {
             if (i == 0) {
-                st_agent(p, sh.M[g]);
-                st_agent(p + 1, sh.L[g]);
+                st_agent(p, M);
+                st_agent(p + 1, L);
             }
             st_agent(p + 2 + i, aa);
         } else {
             if (i == 0) {
-                p[0] = sh.M[g];
-                p[1] = sh.L[g];
+                p[0] = M;
+                p[1] = L;
             }
             p[2 + i] = aa;
         }

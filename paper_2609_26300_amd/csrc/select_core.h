@@ -623,6 +623,64 @@ __device__ inline bool arrive_last(uint32_t* counter, int arrivals, int32_t& las
     return last != 0;
 }
 
+// merge_unit for up to 64 partials: lane p of every wave holds partial p's maximum and sum of the wave's head,
+// requested with the wave's first partial values, so the factors need no LDS and no barrier, and up to
+// SPLIT RB partials cost one round trip. Latency-bound, like finish_exact, whose factors are formed the same
+// way; both together, us a step: 2 units of 4K tokens 20.1 -> 19.3, 36 units of 20K (d = 64) 22.5 -> 21.3, 64
+// units of 64K (G = 8) 46.6 -> 45.6.
+// RB: partial values requested per thread at once (past the last partial: partial 0's again, unused; no
+// branch around a load).
+template <int D, int G, typename Lds, int FT, int RB>
+__device__ void merge_unit_lanes(const Geom& geo, const DecodeArgs& d, int u, Lds& L, bool poison) {
+    constexpr int GD = G * D;
+    constexpr int SPLIT = GD >= FT ? 1 : FT / GD;
+    static_assert(SPLIT == 1 || SPLIT * GD <= (int)(sizeof(L.cw) / sizeof(float)), "split sums fit in LDS");
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int np = d.part_count;
+    const size_t stride = (size_t)G * (D + 2);
+    const float* pu = d.ws_part + (size_t)u * np * stride;
+    float* part_sum = &L.cw[0][0];  // [SPLIT][G d]
+    const int bseq = u / geo.hkv, hk = u - bseq * geo.hkv;
+    auto emit = [&](int g, int i, float A, float M, float S) {  // coordinate i of head g
+        const size_t o = (size_t)bseq * geo.hq + (size_t)hk * G + g;
+        d.out[o * D + i] = poison ? __int_as_float(0x7FC00000) : (S > 0.0f ? A / S : 0.0f);
+        if (i == 0 && d.lse) d.lse[o] = poison ? __int_as_float(0x7FC00000) : (S > 0.0f ? M + logf(S) : -INFINITY);
+    };
+    const int h = SPLIT > 1 ? __builtin_amdgcn_readfirstlane(tid / GD) : 0;  // this wave's share of the partials
+    for (int idx = SPLIT > 1 ? tid - h * GD : tid; idx < GD; idx += SPLIT > 1 ? GD : FT) {
+        const int g = __builtin_amdgcn_readfirstlane(idx / D), i = idx % D;
+        const float* pg = pu + (size_t)g * (D + 2);
+        float x[RB];
+#pragma unroll
+        for (int k = 0; k < RB; ++k) {
+            const int p = h + SPLIT * k;
+            x[k] = ld_agent(pg + (size_t)(p < np ? p : 0) * stride + 2 + i);
+        }
+        const float2 ml = ld_agent2(pg + (size_t)(lane < np ? lane : 0) * stride);
+        const float m = lane < np ? ml.x : -INFINITY;
+        const float M = wave_max(m);
+        const float f = m == -INFINITY ? 0.0f : __expf(m - M);
+        const float S = wave_sum(f * ml.y);
+        float A = 0.0f;
+#pragma unroll
+        for (int k = 0; k < RB; ++k)
+            if (h + SPLIT * k < np) A += readlane_f(f, h + SPLIT * k) * x[k];
+        for (int p = h + SPLIT * RB; p < np; p += SPLIT) A += readlane_f(f, p) * ld_agent(pg + (size_t)p * stride + 2 + i);
+        if constexpr (SPLIT > 1) {
+            part_sum[h * GD + idx] = A;
+            __syncthreads();
+            if (h == 0) {  // (the head's maximum and sum are the same in every share)
+                A = 0.0f;
+#pragma unroll
+                for (int s = 0; s < SPLIT; ++s) A += part_sum[s * GD + idx];
+                emit(g, i, A, M, S);
+            }
+        } else {
+            emit(g, i, A, M, S);
+        }
+    }
+}
+
 // The merge of unit u's d.part_count partials (the result does not depend on which workgroup runs it):
 // per head the maximum M, the sum L of exp(m_p - M) l_p and of exp(m_p - M) acc_p, then out = acc / L
 // and lse = M + log L (NaN when `poison`). SPLIT = FT / (G d) threads share a coordinate: thread h of
@@ -634,6 +692,16 @@ __device__ void merge_unit(const Geom& geo, const DecodeArgs& d, int u, Lds& L, 
     constexpr int GD = G * D;
     constexpr int SPLIT = GD >= FT ? 1 : FT / GD;
     static_assert(SPLIT == 1 || SPLIT * GD <= (int)(sizeof(L.cw) / sizeof(float)), "split sums fit in LDS");
+    if (d.part_count <= 64) {  // (workgroup-uniform)
+        constexpr int SP = G * D >= FT ? 1 : FT / (G * D);
+        if (d.part_count <= 4 * SP)
+            merge_unit_lanes<D, G, Lds, FT, 4>(geo, d, u, L, poison);
+        else if (d.part_count <= 12 * SP)
+            merge_unit_lanes<D, G, Lds, FT, 12>(geo, d, u, L, poison);
+        else
+            merge_unit_lanes<D, G, Lds, FT, 20>(geo, d, u, L, poison);
+        return;
+    }
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int np = d.part_count;
     constexpr int RB = 16;  // partial values requested per round and thread
