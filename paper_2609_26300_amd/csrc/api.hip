@@ -233,6 +233,21 @@ bool one_group_path(const Geom& g, int path, int* st) {
     return path == COMPKV_SELECT_ONE_GROUP && fits;
 }
 
+// Workgroups per unit of the 512-thread form on short units: one per ~200 rows of 4 d bytes (mean values and
+// exact tokens; measured best: 8 units of 3104 rows 17 of 5 / 9 / 12 / 17 / 24, 16 units of 1024 rows 5 to 9, 2
+// units of 512 rows 3). Then by the exact share, which its eight waves attend in rounds of 128 tokens: up to a
+// third more workgroups where that saves a round, else as few as keep the same rounds. At most as many
+// partials as the chunked shape may write.
+int brief_workgroups(const Geom& g, int keff, int xmax) {
+    auto rounds = [&](int p) { return ceil_div((long long)ceil_div(keff, p) * g.B, 128); };
+    const int limit = score_shape(g).nchunks + 1 + sparse_shape(g, keff).n_exact;
+    int p = std::max(2, std::min((int)((xmax + (long long)keff * g.B + 100) / 200), limit));
+    for (int q = p; q <= std::min(p + 3 * p / 10, limit); ++q)
+        if (rounds(q) < rounds(p)) return q;
+    while (p > 2 && rounds(p) > 1 && rounds(p - 1) == rounds(p)) --p;
+    return p;
+}
+
 // Shape of the fused step's selection + exact launch: items of up to select_exact_waves() tiles of 16
 // tokens.
 SxShape sx_shape(const Geom& g, int nchunks, int K) {
@@ -258,19 +273,27 @@ SxShape sx_shape(const Geom& g, int nchunks, int K) {
                       eb <= compkv::decode_max_eb() && n_exact <= compkv::decode_max_items() && cb <= cbmax &&
                       n_comp + n_exact <= compkv::decode_max_partials() &&
                       (n_comp + n_exact) * g.G <= compkv::select_exact_merge_terms();
-    // one-selector launch: per unit one selector and P - 1 workers, compensation shares of at least 128
-    // blocks, every workgroup resident at once. Workgroups of 1024 threads, one per CU; where these would
-    // be fewer than two per unit (more than half as many units as CUs), of 512 threads, two per CU, so
-    // that a unit keeps its worker and one workgroup's loads overlap the other's selection (256 units of up
-    // to 8K tokens: 61 us a step against 78 for the four separate launches; 160 units 51 against 59; with
-    // two 1024-thread workgroups per unit the larger form stays better at long contexts: 128 units of 16K
-    // 54 against 56 us but 32 units of 128K 49 against 46). Its selection holds at most
-    // 16 keys per thread (4 with logit terms).
-    const bool small = 2 * g.units() > resident && (g.G != 8 || xmax <= 2048);
+    // one-selector launch: per unit one selector and P - 1 workers, every workgroup resident at once: of 1024
+    // threads, one per CU, with compensation shares of at least 128 blocks; or of 512 threads, two per CU.
+    // The 512-thread form serves
+    //  * more than half as many units as CUs, so that a unit keeps its worker and one workgroup's loads
+    //    overlap the other's selection (256 units of up to 8K tokens: 61 us a step against 78 for the four
+    //    separate launches; 160 units 51 against 59);
+    //  * units of up to 2048 blocks, whose step is a chain of short phases that eight waves pass through
+    //    faster than sixteen, with more workgroups per unit (below; us a step, 1024 / 512 threads: 8 units
+    //    of 32K tokens in 1024 blocks 24.9 / 22.3, of 16K in 512 25.3 / 21.5, of 64K in 2048 25.3 / 23.2,
+    //    2 units of 4K 19.3 / 17.4, 32 units of 4K 22.9 / 20.8, 96 units of 16K 54.8 / 47.2, 64 units of 64K
+    //    55.3 / 54.3). With eight heads per unit up to 32 units of 1024 blocks (16 units of 16K 26.4 / 24.5,
+    //    but 64 units of 64K, where its selection holds up the stream, 45.5 / 47.3).
+    // At more blocks the 1024-thread form's selection is faster (8 units of 128K 28.1 / 31.7).
+    const bool many = 2 * g.units() > resident && (g.G != 8 || xmax <= 2048);
+    const bool brief = g.G == 8 ? xmax <= 1024 && g.units() <= 32 : xmax <= 2048;
+    const bool small = many || brief;
     const int wt = small ? 512 : 1024;
     const int wresident = small ? compkv::select_exact_slots(g, dyn, wt) : resident;
     const int wper = std::max(1, wresident / std::max(1, g.units()));
     int P = std::min(wper, std::max(1 + ceil_div(xmax, 128), small ? ceil_div((long long)keff * g.B, 256) : 0));
+    if (brief && !many) P = std::max(2, std::min(wper, brief_workgroups(g, keff, xmax)));
     P = std::max(P, 1 + ceil_div(xmax, cbmax));
     P = std::max(P, ceil_div(keff, compkv::decode_max_eb()));
     const int wcb = ceil_div(xmax, std::max(1, P - 1));
@@ -284,8 +307,10 @@ SxShape sx_shape(const Geom& g, int nchunks, int K) {
     // bytes each): spread over all of the unit's workgroups, the exact share then outweighs the repeated
     // selections it saves. Where the mean values dominate, the form with compensation workgroups that
     // stream from the start while the item workgroups select is faster (measured: 128K layer 26.9 vs
-    // 28.6 us; wide GQA 33.3 vs 29.9 us; 32K layer 18.3 vs 18.5 us)
-    const bool work = work_fits && ((long long)xmax <= (long long)keff * g.B || !items_round);
+    // 28.6 us; wide GQA 33.3 vs 29.9 us; 32K layer 18.3 vs 18.5 us). On few short units the 512-thread
+    // form is faster than both (2 units of 1500 blocks, 512 selected tokens: 21.7 -> 19.7 us a step,
+    // 8 units of 400 blocks, 256 tokens 20.7 -> 19.2; 64 units of 2048 blocks, 512 tokens 45.4 / 45.7)
+    const bool work = work_fits && ((brief && g.units() <= 32) || (long long)xmax <= (long long)keff * g.B || !items_round);
     return {eb, n_exact, cb, n_comp, fits, work || items_round, work, wt, P, web, wcb};
 }
 

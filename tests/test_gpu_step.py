@@ -244,13 +244,19 @@ def test_step_stays_within_workspace(name, path):
         assert torch.equal(r[k], ref[k]), k
 
 
-# more than half as many units as compute units: the fused launch's 512-thread form (two or three workgroups
-# per unit), on lengths from empty to full, with a budget above the shortest sequences' blocks; 16 query
-# heads on one KV head pair d = 64 (G = 8), and unit counts that do not fill whole rounds of eight
+# the fused launch's 512-thread form: more than half as many units as compute units (two or three workgroups per
+# unit), on lengths from empty to full, with a budget above the shortest sequences' blocks, G = 8 and unit
+# counts that do not fill whole rounds of eight; and few short units (up to 20 workgroups each) at the edges of its
+# keys per thread (512, 1024 and 2048 blocks) and of the 1024-thread form past them
 @pytest.mark.parametrize("batch,heads,d,B,context,budget", [(65, (8, 2), 128, 16, 1030, 12), (70, (16, 2), 64, 48, 2500, 20),
-                                                            (129, (1, 1), 128, 1, 700, 130), (128, (4, 2), 128, 32, 900, 9)])
-def test_step_many_units(batch, heads, d, B, context, budget):
+                                                            (129, (1, 1), 128, 1, 700, 130), (128, (4, 2), 128, 32, 900, 9),
+                                                            (1, (8, 2), 128, 1, 512, 200), (1, (8, 2), 128, 1, 513, 40),
+                                                            (1, (4, 4), 64, 1, 1024, 33), (2, (8, 1), 128, 1, 1025, 130),
+                                                            (1, (2, 1), 128, 1, 2048, 300), (1, (4, 1), 128, 1, 2049, 40),
+                                                            (1, (16, 2), 128, 2, 2047, 24), (6, (8, 2), 64, 16, 4000, 60)])
+def test_step_small_workgroups(batch, heads, d, B, context, budget):
     lens = [context, 0, 1, B, B + 1, context - 1] + [1 + (37 * i) % context for i in range(6, batch)]
+    lens = lens[:batch]
     c = Case(TINY.with_(batch=batch, n_q_heads=heads[0], n_kv_heads=heads[1], head_dim=d, block_size=B, context=context,
                         budget_blocks=budget, seed=61), seq_lens=lens)
     c.run_all()
