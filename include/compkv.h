@@ -141,8 +141,8 @@ typedef struct compkv_select_params {
  *              most 8192 blocks; otherwise, and in compkv_score_select, as CHUNKED.
  *   AUTO:      in compkv_score_select, ONE_GROUP when a unit holds at most 256 blocks (one workgroup
  *              then reads every summary in a single round of loads), else CHUNKED. In
- *              compkv_decode_step, CHUNKED_EXACT when all of its workgroups are resident at once (at
- *              most one per compute unit), else ONE_GROUP when a unit holds at most 256 blocks, else
+ *              compkv_decode_step, CHUNKED_EXACT when all of its workgroups are resident at once (one
+ *              of 1024 or two of 512 threads per compute unit), else ONE_GROUP when a unit holds at most 256 blocks, else
  *              CHUNKED.
  */
 #define COMPKV_SELECT_AUTO 0
