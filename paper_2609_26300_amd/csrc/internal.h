@@ -8,7 +8,7 @@
 
 namespace compkv {
 
-constexpr int kThreads = 256;  // every kernel runs 256-thread workgroups (4 wave64)
+constexpr int kThreads = 256;  // threads of a scoring, summary or merge workgroup (4 wave64)
 
 // Shape of one call after host validation. The K/V cache is either contiguous per unit
 // ([units][cap][D], bpp == 0) or paged: [npages][hkv][bpp * B][D] with table[bseq][pps] mapping a
@@ -185,7 +185,8 @@ hipError_t launch_select_exact(const Geom& g, ScoreArgs a, const DecodeArgs& d, 
 // the same step with one selector per unit and P - 1 workers (compensation share d.cb, then exact share
 // d.eb once the selection word is set): P workgroups per unit, all resident at once (checked by the
 // caller with select_exact_slots); one partial per workgroup (d.part_count = P, d.part_base = 0: a
-// worker's compensation partial joins its exact one); hipErrorInvalidValue outside its limits
+// worker's compensation partial joins its exact one); workgroups of `threads` (1024 or 512) threads;
+// hipErrorInvalidValue outside its limits
 hipError_t launch_select_work(const Geom& g, ScoreArgs a, const DecodeArgs& d, int P, int threads, hipStream_t s);
 int select_exact_max_budget();
 int select_exact_waves();
