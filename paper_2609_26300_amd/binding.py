@@ -140,6 +140,7 @@ _host_call = None
 _entries: tuple = (None, ())  # the library the addresses belong to, the functions' addresses
 _specs: dict = {}  # what each argument has to be, by the call's kind, the dims' values and the budget
 _MOST_SPECS = 256
+_DIMS_INTS = CompkvDims.block_table.offset  # bytes of the dims' integers (all that the specs depend on)
 
 
 def _load_host():
@@ -164,7 +165,7 @@ def _call(kind, dims, K, args):
         _load_host()
     if _entries[0] is not lib:
         _entries = (lib, tuple(ctypes.cast(getattr(lib, f), _vp).value for f in _ENTRIES))
-    key = (kind, bytes(dims), K)
+    key = (kind, bytes(dims)[:_DIMS_INTS], K)
     spec = _specs.get(key)
     if spec is None:
         if len(_specs) >= _MOST_SPECS:

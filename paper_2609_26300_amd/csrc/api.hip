@@ -254,13 +254,16 @@ SxShape sx_shape(const Geom& g, int nchunks, int K) {
     const int xmax = g.xmax();
     const int keff = std::max(1, std::min(K, xmax));
     const int cus = device_cus(0);
-    // one resident round of workgroups (two per CU): up to half of a unit's share goes to compensation
+    // one resident round of workgroups (one per CU): up to half of a unit's share goes to compensation
     // workgroups (of at least 128 and at most select_exact_max_cb() blocks each: few partials to merge)
     // and the rest to exact items, the smallest of at least 64 tokens that fit it (an item of more
     // tiles than the workgroup has waves takes several rounds of its waves), so that each CU streams
     // mean values while its item workgroup selects
     const size_t dyn = ((size_t)2 * (nchunks + 1) * g.G + (size_t)xmax) * sizeof(float);
-    const int resident = compkv::select_exact_slots(g, dyn, 1024);
+    // (never more than one 1024-thread workgroup per CU, whatever the registers of a head size allow: the shapes
+    // below, and with them the workspace a step needs, were chosen and measured so)
+    const int slots1024 = compkv::select_exact_slots(g, dyn, 1024);
+    const int resident = cus > 0 ? std::min(slots1024, cus) : slots1024;
     const int per = std::max(1, resident / std::max(1, g.units()));
     const int cbmax = compkv::select_exact_max_cb();
     int n_comp = std::max(1, std::min(per / 2, ceil_div(xmax, 128)));
