@@ -260,10 +260,7 @@ SxShape sx_shape(const Geom& g, int nchunks, int K) {
     // tiles than the workgroup has waves takes several rounds of its waves), so that each CU streams
     // mean values while its item workgroup selects
     const size_t dyn = ((size_t)2 * (nchunks + 1) * g.G + (size_t)xmax) * sizeof(float);
-    // (never more than one 1024-thread workgroup per CU, whatever the registers of a head size allow: the shapes
-    // below, and with them the workspace a step needs, were chosen and measured so)
-    const int slots1024 = compkv::select_exact_slots(g, dyn, 1024);
-    const int resident = cus > 0 ? std::min(slots1024, cus) : slots1024;
+    const int resident = compkv::select_exact_slots(g, dyn, 1024);
     const int per = std::max(1, resident / std::max(1, g.units()));
     const int cbmax = compkv::select_exact_max_cb();
     int n_comp = std::max(1, std::min(per / 2, ceil_div(xmax, 128)));

@@ -394,13 +394,15 @@ int decode_max_cb() { return kCbMax; }
 int decode_max_eb() { return kMaxEb; }
 int decode_max_row_bases() { return kMaxRowBase; }
 
+// Two item workgroups per CU: the launch shapes, and with them the workspace that a step needs, were chosen for
+// two, also where a head size's registers would allow a third.
 template <int D>
 int item_slots_d(const Geom& g) {
     switch (g.G) {
-        case 1: return resident_slots(decode_items_kernel<D, 1>, kItemThreads);
-        case 2: return resident_slots(decode_items_kernel<D, 2>, kItemThreads);
-        case 4: return resident_slots(decode_items_kernel<D, 4>, kItemThreads);
-        default: return resident_slots(decode_items_kernel<D, 8>, kItemThreads);
+        case 1: return resident_slots(decode_items_kernel<D, 1>, kItemThreads, 2);
+        case 2: return resident_slots(decode_items_kernel<D, 2>, kItemThreads, 2);
+        case 4: return resident_slots(decode_items_kernel<D, 4>, kItemThreads, 2);
+        default: return resident_slots(decode_items_kernel<D, 8>, kItemThreads, 2);
     }
 }
 int decode_item_slots(const Geom& g) { return g.D == 128 ? item_slots_d<128>(g) : item_slots_d<64>(g); }

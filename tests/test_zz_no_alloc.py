@@ -67,3 +67,10 @@ def test_noalloc_matches_workspace_step_twice():
     """A 32K layer of 8 units, then a smaller 4K case of 2 units on the scratch it left behind."""
     _compare(Case(LLAMA.with_(context=32768, seed=41)))
     _compare(Case(TINY.with_(context=3000, budget_blocks=24, seed=42)))
+
+
+def test_small_heads_stay_within_the_scratch():
+    """A d = 64 shape close to the fixed scratch: its workspace is sized for two item workgroups per compute unit,
+    whatever the item kernel's registers would allow, so the allocation-free step keeps accepting it."""
+    d = P.make_dims(20, 8, 4, 64, 24, 4, 183458)
+    assert P.compkv_workspace_bytes(d, 31, P.COMPKV_WS_DECODE_STEP) <= P.compkv_decode_step_noalloc_limit()
