@@ -193,7 +193,6 @@ __device__ void block_stats_from(const BlockSrc& b, BlockRows& R, int r, int lay
 // the four waves' sums, the butterflies over the row groups, the pair sums and the group butterflies over
 // lanes = pairs. So its results are bit-identical to block_stats_from's, which the append and the fused
 // step keep using.
-constexpr int kWaveStepsMax = 4;
 template <int D>
 constexpr int wave_stats_max_rows(int steps) {
     return steps * 4 * (64 / (D / 8));
