@@ -245,7 +245,8 @@ __device__ __forceinline__ void pin_rows(WaveRows<NS>& R) {
 
 // Adds the rows to the lane's per-virtual-wave sums s[v][8] (kDev: the squared deviations from mk instead).
 // A row past the block (a reload of row 0) enters with factor 0: fma(1, x, s) rounds like s + x, so the mask
-// costs one instruction per row instead of one per value, and no second code path.
+// costs one instruction per row instead of one per value. Where row 0's value (or its square) is not finite,
+// the product is NaN and so is the sum: the caller then takes wave_block_alone.
 template <int D, int NS, bool kDev>
 __device__ __forceinline__ void add_wave_rows(const WaveRows<NS>& R, int nb, int s0, const float (&mk)[8], float (&s)[4][8]) {
     constexpr int LPR = D / 8, RPW = 64 / LPR, RPG = 4 * RPW;
@@ -269,15 +270,20 @@ __device__ __forceinline__ void add_wave_rows(const WaveRows<NS>& R, int nb, int
         }
 }
 
+template <int D>
+__device__ __forceinline__ void add_row_groups(float (&t)[8]) {
+#pragma unroll
+    for (int off = D / 8; off < 64; off <<= 1)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) t[e] = xor_add(t[e], off);
+}
+
 // ((w0 + w1) + (w2 + w3)), then over the row groups: every lane of a column holds the column's total
 template <int D>
 __device__ __forceinline__ void total_wave_rows(const float (&s)[4][8], float (&t)[8]) {
 #pragma unroll
     for (int e = 0; e < 8; ++e) t[e] = (s[0][e] + s[1][e]) + (s[2][e] + s[3][e]);
-#pragma unroll
-    for (int off = D / 8; off < 64; off <<= 1)
-#pragma unroll
-        for (int e = 0; e < 8; ++e) t[e] = xor_add(t[e], off);
+    add_row_groups<D>(t);
 }
 
 __device__ __forceinline__ void zero_sums(float (&s)[4][8]) {
@@ -285,6 +291,14 @@ __device__ __forceinline__ void zero_sums(float (&s)[4][8]) {
     for (int v = 0; v < 4; ++v)
 #pragma unroll
         for (int e = 0; e < 8; ++e) s[v][e] = 0.0f;
+}
+
+// Zero, or NaN where one of the lane's sums is not finite
+__device__ __forceinline__ float finite_mark(const float (&t)[8]) {
+    float m = 0.0f;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) m = __builtin_fmaf(t[e], 0.0f, m);
+    return m;
 }
 
 // The grouped variances from the coordinates' sums of squared deviations m2 (lane li: 8 li .. 8 li + 7)
@@ -320,6 +334,51 @@ __device__ __forceinline__ void store_wave_variances(float (&m2)[8], int nb, int
     const int w = (D / 2) / r;
     for (int off = 1; off < w; off <<= 1) e2 = xor_add(e2, off);
     if (in && lane % w == 0) dv_out[lane / w] = e2 / (fn * (float)(D / r));
+}
+
+// The summary of one block by one wave from the block's own rows alone, read again from memory, in the same
+// order of sums: for the rare wave that met a block whose sums are not finite.
+template <int D>
+__device__ void wave_block_alone(const uint16_t* Kb, const uint16_t* Vb, int nb, int r, int layout,
+                                    float* __restrict__ km_out, float* __restrict__ dv_out, float* __restrict__ vm_out) {
+#pragma clang fp contract(off)  // (the rounded square is added, as in the workgroup routine: the same bits)
+    constexpr int LPR = D / 8, RPW = 64 / LPR, RPG = 4 * RPW;
+    const int lane = threadIdx.x & 63, ro = lane / LPR, li = lane % LPR;
+    float mean[8] = {0, 0, 0, 0, 0, 0, 0, 0}, t[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+#pragma unroll 1
+    for (int pass = 0; pass < 3; ++pass) {  // values, keys, the keys' squared deviations
+        const uint16_t* p = pass == 0 ? Vb : Kb;
+        float pair[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+#pragma unroll 1
+        for (int v = 0; v < 4; ++v) {  // (w0 + w1) + (w2 + w3)
+            float s[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+#pragma unroll 1
+            for (int j = v * RPW + ro; j < nb; j += RPG) {
+                float f[8];
+                unpack_bf16x8(*reinterpret_cast<const uint4*>(p + (size_t)j * D + li * 8), f);
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                    const float dev = f[e] - mean[e];
+                    s[e] += pass == 2 ? __fmul_rn(dev, dev) : f[e];
+                }
+            }
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                t[e] = v == 1 ? pair[e] + s[e] : v == 3 ? t[e] + (pair[e] + s[e]) : t[e];
+                pair[e] = s[e];
+            }
+        }
+        add_row_groups<D>(t);
+        if (pass == 2) break;
+        divide8(t, nb);
+        float* out = pass == 0 ? vm_out : km_out;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            mean[e] = t[e];
+            if (ro == 0) out[li * 8 + e] = t[e];
+        }
+    }
+    store_wave_variances<D>(t, nb, r, layout, dv_out);
 }
 
 template <int D>

@@ -60,9 +60,12 @@ __global__ __launch_bounds__(kThreads) void build_stats_kernel(Geom g, StatsArgs
 // around a load (the registers are loaded in place). With the masks as factors, one butterfly per sum and
 // the exact reciprocal of a power-of-two count a block takes 890 vector instructions. One layer of 32K tokens
 // x 8 KV heads, d = 128, blocks of 32: 39.1 -> 29.7 us (143 MB, 4.8 TB/s); 128K x 4: 490 -> 448 us (5.1 TB/s);
-// blocks of 16: 923 -> 460 us; d = 64: 532 -> 206 us.
+// blocks of 16: 923 -> 460 us; d = 64: 532 -> 206 us. The test for sums that are not finite costs -4 to +4%
+// (32K x 8 heads 32.9 -> 33.8 us, blocks of 24 64.4 -> 61.8, d = 64 55.3 -> 57.3); clearing each row past a block
+// instead up to 12%. (Five workgroups per CU asked for: without it the recomputation after the loop takes the
+// small form's registers past that.)
 template <int D, int NS, int VS>
-__global__ __launch_bounds__(kThreads) void build_stats_wave_kernel(Geom g, StatsArgs a) {
+__global__ __launch_bounds__(kThreads, NS == 1 ? 5 : 2) void build_stats_wave_kernel(Geom g, StatsArgs a) {
     constexpr int WPG = kThreads / 64, LPR = D / 8;
     static_assert(NS % VS == 0, "whole batches of values");
     const int lane = threadIdx.x & 63, ro = lane / LPR, li = lane % LPR;
@@ -74,7 +77,9 @@ __global__ __launch_bounds__(kThreads) void build_stats_wave_kernel(Geom g, Stat
         int nb;  // 0: no block (past the sequence, or past the last)
     };
     // (a wave's index in a scalar register: the whole item is wave-uniform)
-    int flat = blockIdx.x * WPG + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int first = blockIdx.x * WPG + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    int flat = first;
+    bool redo = false;
     auto next_item = [&]() {  // the wave's next block within its sequence
         for (; flat < total; flat += nwaves) {
             const int u = flat / xmax, b = flat - u * xmax;
@@ -110,6 +115,7 @@ __global__ __launch_bounds__(kThreads) void build_stats_wave_kernel(Geom g, Stat
                 load_wave_rows<D, VS>(a.V + nxt.row0 * D, nxt.nb, 0, V);
         }
         total_wave_rows<D>(s, t);
+        redo |= __any(finite_mark(t) != 0.0f);  // (NaN differs from 0)
         divide8(t, nb);
         if (ro == 0) {
             float4* vo = reinterpret_cast<float4*>(a.vmean + cur.blk * D + li * 8);
@@ -133,10 +139,19 @@ __global__ __launch_bounds__(kThreads) void build_stats_wave_kernel(Geom g, Stat
         __builtin_amdgcn_sched_barrier(0);
         load_wave_rows<D, NS>(a.K + nxt.row0 * D, nxt.nb, 0, K);
         total_wave_rows<D>(s, t);
+        // (a mean key that is not finite leaves no squared deviation finite: this covers the keys' sums too)
+        redo |= __any(finite_mark(t) != 0.0f);
         store_wave_variances<D>(t, nb, g.r, g.layout, a.dvar + cur.blk * g.r);
-        if (!more) return;
+        if (!more) break;
         cur = nxt;
     }
+    if (!redo) return;
+    // some block's sums were not finite, for which a row past a block may be to blame: the wave's blocks again, from
+    // their own rows alone (here, where no next block is held, so that the loop above keeps its registers)
+    flat = first;
+    for (cur = next_item(); cur.nb != 0; cur = next_item())
+        wave_block_alone<D>(a.K + cur.row0 * D, a.V + cur.row0 * D, cur.nb, g.r, g.layout, a.kmean + cur.blk * D,
+                               a.dvar + cur.blk * g.r, a.vmean + cur.blk * D);
 }
 
 // grid = (units): workgroup u recomputes block n / B with the new row n = seq_lens (before the append)

@@ -260,3 +260,43 @@ def test_build_block_edges(d, B, r, layout):
     torch.cuda.synchronize()
     for k in ("kmean", "dvar", "vmean"):
         assert torch.equal(getattr(a, k), getattr(s, k)), k
+
+
+# keys and values that are infinite, or whose squared deviations overflow, in row 0 of partly filled blocks (the row
+# that the wave build loads in place of a row past the block): the sums in numpy's float32, whose infinities and
+# NaNs depend on no order, and bit for bit (NaN for NaN) the append's
+@pytest.mark.parametrize("d,B,r", [(128, 16, 128), (128, 24, 4), (128, 48, 4), (64, 32, 1), (64, 100, 64)])
+def test_build_non_finite_rows(d, B, r):
+    import paper_2609_26300_amd as P
+
+    lens = [2 * B - 1, B + 3, 2, B + 1]
+    c = Case(TINY.with_(batch=4, head_dim=d, block_size=B, context=2 * B, n_var_groups=r, budget_blocks=2, seed=73),
+             seq_lens=lens)
+    inf = float("inf")
+    for row in (0, B):
+        c.K[0, :, row, 3], c.V[0, :, row, 5], c.V[0, :, row, 6] = inf, -inf, 3e38
+        c.K[1, :, row, 1], c.K[1, :, row, d - 1] = 3e20, -3e30
+    c.K[2, :, 0, 0], c.V[2, :, 0, d - 1] = float("nan"), float("nan")
+    c.K[3, :, :2, 7], c.V[3, :, :2, 7] = 3e38, 3e38  # (finite rows whose sum overflows)
+    s = c.build_stats()
+    before = (c.sl - 1).to(torch.int32)
+    kn = torch.stack([c.K[b, :, n - 1] for b, n in enumerate(lens)]).contiguous()
+    vn = torch.stack([c.V[b, :, n - 1] for b, n in enumerate(lens)]).contiguous()
+    a = P.alloc_summaries(c.dims)
+    P.compkv_build_stats(c.dims, c.K, c.V, before, a.kmean, a.dvar, a.vmean)
+    P.compkv_append_stats(c.dims, c.K, c.V, kn, vn, before, a.kmean, a.dvar, a.vmean)
+    torch.cuda.synchronize()
+    for k in ("kmean", "dvar", "vmean"):
+        assert torch.equal(torch.nan_to_num(getattr(a, k), nan=7e37, posinf=8e37, neginf=9e37),
+                           torch.nan_to_num(getattr(s, k), nan=7e37, posinf=8e37, neginf=9e37)), k
+    with np.errstate(all="ignore"):
+        for b, n in enumerate(lens):
+            for x in range(-(-n // B)):
+                K = c.K[b, :, x * B:min(n, (x + 1) * B)].float().cpu().numpy()
+                V = c.V[b, :, x * B:min(n, (x + 1) * B)].float().cpu().numpy()
+                km, vm = K.sum(1) / np.float32(K.shape[1]), V.sum(1) / np.float32(K.shape[1])
+                m2 = ((K - km[:, None]) ** 2).sum(1)
+                for got, want in ((s.kmean, km), (s.vmean, vm)) + (((s.dvar, m2),) if r == d else ()):
+                    got = got[b, :, x].cpu().numpy()
+                    assert np.array_equal(np.isnan(got), np.isnan(want)) and np.array_equal(np.isposinf(got), np.isposinf(want))
+                    assert np.array_equal(np.isneginf(got), np.isneginf(want))
