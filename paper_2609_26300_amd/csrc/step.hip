@@ -561,20 +561,22 @@ __global__ __launch_bounds__(kFinThreads) void step_stream_kernel(Geom geo, Scor
         return;
     }
     w -= units;
+    int u;
     if (w < units * d.n_comp) {  // compensation
-        const int u = w / d.n_comp, j = w - u * d.n_comp;
+        u = w / d.n_comp;
+        const int j = w - u * d.n_comp;
         const int n = clamp_len(d.seq_lens[u / geo.hkv], geo.max_seq);
         const int xs = max(0, (n + geo.B - 1) / geo.B - 1);
         const int c0 = min(j * d.cb, xs), c1 = min(c0 + d.cb, xs);
         constexpr int ROWS = 128 / (kFinThreads / (D / 4));  // batches of 128 rows
         stream_compensation<D, G, ROWS>(geo, d, u, n, c0, c1, L.u.sx,
                                         d.ws_part + ((size_t)u * d.part_count + 1 + j) * G * (D + 2));
-        step_arrive<D, G>(geo, d, u, state + 4 * u, L);
-        return;
+    } else {
+        w -= units * d.n_comp;
+        u = w / d.n_exact;
+        step_exact<D, G>(geo, a, d, u, w - u * d.n_exact, state + 4 * u, L.u.sx);
     }
-    w -= units * d.n_comp;
-    const int u = w / d.n_exact, item = w - u * d.n_exact;
-    step_exact<D, G>(geo, a, d, u, item, state + 4 * u, L.u.sx);
+    // (one copy of the merge: a second one spilled 368 bytes at G = 4, d = 128, a 32-unit step of 128K tokens 60 -> 93 us)
     step_arrive<D, G>(geo, d, u, state + 4 * u, L);
 }
 
