@@ -293,12 +293,10 @@ __device__ __forceinline__ void zero_sums(float (&s)[4][8]) {
         for (int e = 0; e < 8; ++e) s[v][e] = 0.0f;
 }
 
-// Zero, or NaN where one of the lane's sums is not finite
-__device__ __forceinline__ float finite_mark(const float (&t)[8]) {
-    float m = 0.0f;
-#pragma unroll
-    for (int e = 0; e < 8; ++e) m = __builtin_fmaf(t[e], 0.0f, m);
-    return m;
+// Whether one of the wave's sums is not finite (or their total overflows, which is harmless: see the caller)
+__device__ __forceinline__ bool any_not_finite(const float (&t)[8]) {
+    const float x = ((t[0] + t[1]) + (t[2] + t[3])) + ((t[4] + t[5]) + (t[6] + t[7]));
+    return __any(!(fabsf(x) < INFINITY));
 }
 
 // The grouped variances from the coordinates' sums of squared deviations m2 (lane li: 8 li .. 8 li + 7)

@@ -56,17 +56,20 @@ __global__ __launch_bounds__(kThreads) void build_stats_kernel(Geom g, StatsArgs
 // barrier, no LDS; bit-identical to the workgroup routine), consecutive waves taking consecutive blocks.
 // HBM-bound, with the vector ALUs ~40% busy: the wave holds the block's keys (needed twice) and its values, VS
 // steps at a time; the next block's values are requested as soon as this block's are added and its keys as
-// soon as the squared deviations are, so loads stay in flight while the wave computes, and no branch lies
-// around a load (the registers are loaded in place). With the masks as factors, one butterfly per sum and
+// soon as the squared deviations are, so loads stay in flight while the wave computes (the registers are loaded in
+// place). With the masks as factors, one butterfly per sum and
 // the exact reciprocal of a power-of-two count a block takes 890 vector instructions. One layer of 32K tokens
-// x 8 KV heads, d = 128, blocks of 32: 39.1 -> 29.7 us (143 MB, 4.8 TB/s); 128K x 4: 490 -> 448 us (5.1 TB/s);
-// blocks of 16: 923 -> 460 us; d = 64: 532 -> 206 us. The test for sums that are not finite costs -4 to +4%
-// (32K x 8 heads 32.9 -> 33.8 us, blocks of 24 64.4 -> 61.8, d = 64 55.3 -> 57.3); clearing each row past a block
-// instead up to 12%. (Five workgroups per CU asked for: without it the recomputation after the loop takes the
-// small form's registers past that.)
+// x 8 KV heads, d = 128, blocks of 32: 39.1 -> 29.3 us (143 MB, 4.9 TB/s); 128K x 4: 490 -> 403 us (5.7 TB/s);
+// blocks of 16: 923 -> 430 us; d = 64: 532 -> 206 us. The test for sums that are not finite (partly filled blocks
+// alone) costs up to 3%; clearing each row past a block instead cost up to 12%. (Five workgroups per CU asked for:
+// without it the recomputation after the loop takes the small form's registers past that.)
+// After a wave's last block its first row is requested once more, unused, so that no branch lies around the loads; with
+// the whole block requested again a build of 2048 blocks took 11.9 us against 10.4 and one of 32K from host memory 3.02 ms
+// against 2.48.
 template <int D, int NS, int VS>
 __global__ __launch_bounds__(kThreads, NS == 1 ? 5 : 2) void build_stats_wave_kernel(Geom g, StatsArgs a) {
     constexpr int WPG = kThreads / 64, LPR = D / 8;
+    constexpr int kRows = wave_stats_max_rows<D>(NS);
     static_assert(NS % VS == 0, "whole batches of values");
     const int lane = threadIdx.x & 63, ro = lane / LPR, li = lane % LPR;
     const int xmax = g.xmax();
@@ -101,7 +104,7 @@ __global__ __launch_bounds__(kThreads, NS == 1 ? 5 : 2) void build_stats_wave_ke
     while (true) {
         Item nxt = next_item();
         const bool more = nxt.nb != 0;
-        if (!more) nxt = cur;  // (the last block is requested once more, unused: no branch around the loads)
+        if (!more) nxt = Item{cur.row0, cur.blk, 1};  // (its first row once more, unused)
         const int nb = cur.nb;
         float s[4][8], mk[8], t[8];
         zero_sums(s);
@@ -115,7 +118,7 @@ __global__ __launch_bounds__(kThreads, NS == 1 ? 5 : 2) void build_stats_wave_ke
                 load_wave_rows<D, VS>(a.V + nxt.row0 * D, nxt.nb, 0, V);
         }
         total_wave_rows<D>(s, t);
-        redo |= __any(finite_mark(t) != 0.0f);  // (NaN differs from 0)
+        if (nb < kRows) redo |= any_not_finite(t);
         divide8(t, nb);
         if (ro == 0) {
             float4* vo = reinterpret_cast<float4*>(a.vmean + cur.blk * D + li * 8);
@@ -140,7 +143,7 @@ __global__ __launch_bounds__(kThreads, NS == 1 ? 5 : 2) void build_stats_wave_ke
         load_wave_rows<D, NS>(a.K + nxt.row0 * D, nxt.nb, 0, K);
         total_wave_rows<D>(s, t);
         // (a mean key that is not finite leaves no squared deviation finite: this covers the keys' sums too)
-        redo |= __any(finite_mark(t) != 0.0f);
+        if (nb < kRows) redo |= any_not_finite(t);
         store_wave_variances<D>(t, nb, g.r, g.layout, a.dvar + cur.blk * g.r);
         if (!more) break;
         cur = nxt;
