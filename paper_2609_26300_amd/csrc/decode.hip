@@ -399,10 +399,10 @@ int decode_max_row_bases() { return kMaxRowBase; }
 template <int D>
 int item_slots_d(const Geom& g) {
     switch (g.G) {
-        case 1: return resident_slots(decode_items_kernel<D, 1>, kItemThreads, 2);
-        case 2: return resident_slots(decode_items_kernel<D, 2>, kItemThreads, 2);
-        case 4: return resident_slots(decode_items_kernel<D, 4>, kItemThreads, 2);
-        default: return resident_slots(decode_items_kernel<D, 8>, kItemThreads, 2);
+        case 1: return resident_slots<decode_items_kernel<D, 1>>(kItemThreads, 2);
+        case 2: return resident_slots<decode_items_kernel<D, 2>>(kItemThreads, 2);
+        case 4: return resident_slots<decode_items_kernel<D, 4>>(kItemThreads, 2);
+        default: return resident_slots<decode_items_kernel<D, 8>>(kItemThreads, 2);
     }
 }
 int decode_item_slots(const Geom& g) { return g.D == 128 ? item_slots_d<128>(g) : item_slots_d<64>(g); }

@@ -6,6 +6,8 @@
 #include <cstddef>
 #include <cstdint>
 
+#include "kernel_slots.h"
+
 namespace compkv {
 
 constexpr int kThreads = 256;  // threads of a scoring, summary or merge workgroup (4 wave64)
@@ -208,33 +210,17 @@ int step_stream_max_budget();
 int step_stream_merge_terms();  // partials x heads limit of the in-launch merge
 size_t step_stream_dyn_lds(const Geom& g, int nchunks);
 
-// Resident workgroups of `kern` (`threads` each, no dynamic LDS) on the current device, at most `most` per
-// compute unit; cached per (kernel, device). Not thread-safe on first use per kernel; a race only repeats the
-// same query.
-template <typename Kern>
-int resident_slots(Kern kern, int threads = kThreads, int most = 1 << 10) {
-    constexpr int kSlots = 64;
-    static const void* key_fn[kSlots];
-    static int key_dev[kSlots], value[kSlots], cu_count[kSlots];
+// Resident workgroups of `Kern` (`threads` each, no dynamic LDS) on the current device, at most `most` per
+// compute unit (kernel_slots.h keeps the kernel's occupancy).
+template <auto Kern>
+int resident_slots(int threads = kThreads, int most = 1 << 10) {
     int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess) dev = 0;
-    const void* fn = reinterpret_cast<const void*>(kern);
-    for (int i = 0; i < kSlots; ++i)
-        if (key_fn[i] == fn && key_dev[i] == dev && value[i] > 0 && cu_count[i] > 0)
-            return (value[i] < most ? value[i] : most) * cu_count[i];
-    int per_cu = 0, cus = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kern, threads, 0) != hipSuccess || per_cu < 1)
-        per_cu = 1;
-    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1) cus = 1;
-    for (int i = 0; i < kSlots; ++i)
-        if (key_fn[i] == nullptr) {
-            key_fn[i] = fn;
-            key_dev[i] = dev;
-            cu_count[i] = cus;
-            value[i] = per_cu;
-            break;
-        }
-    return (per_cu < most ? per_cu : most) * cus;
+    if (hipGetDevice(&dev) != hipSuccess) dev = -1;
+    const Occupancy o = kernel_occupancy<Kern>(dev, [&](Occupancy& q) {
+        return hipOccupancyMaxActiveBlocksPerMultiprocessor(&q.per_cu, Kern, threads, 0) == hipSuccess &&
+               hipDeviceGetAttribute(&q.cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess;
+    });
+    return (o.per_cu < most ? o.per_cu : most) * o.cus;
 }
 
 // ------------------------------------------------------------------ device helpers

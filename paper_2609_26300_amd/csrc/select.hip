@@ -666,7 +666,7 @@ __global__ __launch_bounds__(kFinThreads) void unit_select_kernel(Geom geo, Scor
 template <int D, int G, bool kStep, int PMAX, bool kWide>
 void launch_chunks_p(const Geom& g, ScoreArgs a, hipStream_t s) {
     const int grid = (a.nchunks + 1) * g.units();
-    a.tail_first = grid <= resident_slots(score_chunks_kernel<D, G, kStep, PMAX, kWide>);
+    a.tail_first = grid <= resident_slots<score_chunks_kernel<D, G, kStep, PMAX, kWide>>();
     score_chunks_kernel<D, G, kStep, PMAX, kWide><<<dim3(grid), kThreads, 0, s>>>(g, a);
 }
 

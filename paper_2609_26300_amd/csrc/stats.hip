@@ -194,7 +194,7 @@ template <int D, int NS, int VS>
 void launch_build_wave(const Geom& g, const StatsArgs& a, int most, hipStream_t s) {
     const long long total = (long long)g.xmax() * g.units();
     const long long wgs = (total + kThreads / 64 - 1) / (kThreads / 64);
-    const long long slots = resident_slots(build_stats_wave_kernel<D, NS, VS>, kThreads, most);
+    const long long slots = resident_slots<build_stats_wave_kernel<D, NS, VS>>(kThreads, most);
     build_stats_wave_kernel<D, NS, VS><<<dim3((unsigned)(wgs < slots ? wgs : slots)), kThreads, 0, s>>>(g, a);
 }
 
@@ -208,7 +208,7 @@ void launch_build_d(const Geom& g, const StatsArgs& a, hipStream_t s) {
     if (g.B <= wave_stats_max_rows<D>(2)) return launch_build_wave<D, 2, 2>(g, a, 2, s);
     if (g.B <= wave_stats_max_rows<D>(4)) return launch_build_wave<D, 4, 2>(g, a, 2, s);
     const long long total = (long long)g.xmax() * g.units();
-    const long long slots = resident_slots(build_stats_kernel<D>);  // one resident round, grid-stride
+    const long long slots = resident_slots<build_stats_kernel<D>>();  // one resident round, grid-stride
     build_stats_kernel<D><<<dim3((unsigned)(total < slots ? total : slots)), kThreads, 0, s>>>(g, a);
 }
 

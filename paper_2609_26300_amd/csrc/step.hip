@@ -582,7 +582,7 @@ __global__ __launch_bounds__(kFinThreads) void step_stream_kernel(Geom geo, Scor
 
 template <int D, int G>
 int score_slots() {
-    return resident_slots(step_score_kernel<D, G>, kScoreThreads);
+    return resident_slots<step_score_kernel<D, G>>(kScoreThreads);
 }
 
 template <int D, int G>
