@@ -1,4 +1,5 @@
-"""ctypes binding of libcompkv.so: argument marshalling only (see include/compkv.h for semantics)."""
+"""Binding of libcompkv.so (see include/compkv.h for semantics): argument checks and marshalling only, natively
+(csrc/host.cpp) on the usual path and with ctypes for whatever that does not recognise."""
 from __future__ import annotations
 
 import ctypes
@@ -160,6 +161,8 @@ def _load_host():
 def _call(kind, dims, K, args):
     """Status of the call with `args` (after dims), or None where the checks in Python have to decide."""
     global _entries
+    if not isinstance(dims, CompkvDims):
+        return None
     lib = library()
     if _host_call is None:
         _load_host()
@@ -170,7 +173,11 @@ def _call(kind, dims, K, args):
     if spec is None:
         if len(_specs) >= _MOST_SPECS:
             _specs.clear()
-        spec = _specs[key] = _call_spec(kind, dims, K)
+        try:
+            spec = _call_spec(kind, dims, K)
+        except ZeroDivisionError:  # (no shapes follow from these dims)
+            return None
+        _specs[key] = spec
     return _host_call(kind, _entries[1][kind], (ctypes.addressof(dims), *args), spec)
 
 
@@ -182,19 +189,19 @@ def _call_spec(kind, d, K):
     KV, SUM, DV, Q = (bf, cache, False), (f32, summ, False), (f32, dvar, False), (bf, q, False)
     SEQ, NEW = (i32, (d.batch,), False), (bf, new, False)
     SEL, NSEL = (i32, (*units, K), False), (i32, units, False)
-    blk, scores = (*units, d.group, d.xcap), (*units, d.xcap)
     OUT, LSE = (f32, q, False), (f32, q[:2], True)
     if kind == _BUILD:
         return (None, KV, KV, SEQ, SUM, DV, SUM, None)
     if kind == _APPEND:
         return (None, KV, KV, NEW, NEW, SEQ, SUM, DV, SUM, None)
+    if kind == _DENSE:
+        return (None, None, Q, KV, KV, SEQ, OUT, LSE, True, None)
+    blk, scores = (*units, d.group, d.xcap), (*units, d.xcap)
     if kind == _SCORE:
         return (None, None, Q, SUM, DV, SEQ, SEL, NSEL, (f32, blk, True), (f32, scores, True), True, None)
     if kind == _SPARSE:
         return (None, None, Q, KV, KV, (f32, summ, True), (f32, summ, True), (f32, blk, True), SEQ, SEL, NSEL, None, OUT,
                 LSE, True, None)
-    if kind == _DENSE:
-        return (None, None, Q, KV, KV, SEQ, OUT, LSE, True, None)
     step = (None, None, Q, KV, KV, (bf, new, True), (bf, new, True), SEQ, SUM, DV, SUM, SEL, NSEL, (f32, blk, False),
             (f32, scores, True), OUT, LSE)
     return (*step, True, None) if kind == _STEP else (*step, None)
@@ -266,7 +273,8 @@ def _raw_stream(stream):
         if not torch.cuda.is_initialized():
             return None
         return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())  # (the current stream's handle)
-    return _stream(stream)
+    s = _stream(stream)
+    return s if isinstance(s, int) else None
 
 
 def _ws(workspace):
@@ -349,10 +357,11 @@ def compkv_append_stats(dims, k_cache, v_cache, k_new, v_new, seq_lens, kmean, d
 
 def compkv_score_select(dims, params: CompkvSelectParams, q, kmean, dvar, seq_lens, sel, n_sel, blk_logit,
                         scores, workspace, stream=None):
-    st = _call(_SCORE, dims, params.budget_blocks, (ctypes.addressof(params), q, kmean, dvar, seq_lens, sel, n_sel,
-                                                    blk_logit, scores, workspace, _raw_stream(stream)))
-    if st is not None:
-        return _check(st, "compkv_score_select")
+    if isinstance(params, CompkvSelectParams):
+        st = _call(_SCORE, dims, params.budget_blocks, (ctypes.addressof(params), q, kmean, dvar, seq_lens, sel, n_sel,
+                                                        blk_logit, scores, workspace, _raw_stream(stream)))
+        if st is not None:
+            return _check(st, "compkv_score_select")
     _, summ, dv, qs = _shapes(dims)
     f32, i32 = torch.float32, torch.int32
     units = (dims.batch, dims.n_kv_heads)
@@ -371,7 +380,7 @@ def compkv_sparse_decode(dims, scale, q, k_cache, v_cache, vmean, blk_logit, seq
                          lse=None, workspace=None, stream=None, kmean=None):
     """Compensated sparse decode; vmean = blk_logit = None gives the Drop decode. With blk_logit None
     and vmean given, the block-mean logits are recomputed from kmean."""
-    if sel is not None and sel.dim() == 3:
+    if isinstance(sel, torch.Tensor) and sel.dim() == 3 and isinstance(scale, (float, int)):
         K = int(sel.shape[2])
         st = _call(_SPARSE, dims, K, (float(scale), q, k_cache, v_cache, kmean, vmean, blk_logit, seq_lens, sel, n_sel, K,
                                       out, lse, workspace, _raw_stream(stream)))
@@ -395,9 +404,11 @@ def compkv_sparse_decode(dims, scale, q, k_cache, v_cache, vmean, blk_logit, seq
 
 
 def compkv_dense_decode(dims, scale, q, k_cache, v_cache, seq_lens, out, lse=None, workspace=None, stream=None):
-    st = _call(_DENSE, dims, 0, (float(scale), q, k_cache, v_cache, seq_lens, out, lse, workspace, _raw_stream(stream)))
-    if st is not None:
-        return _check(st, "compkv_dense_decode")
+    if isinstance(scale, (float, int)):
+        st = _call(_DENSE, dims, 0, (float(scale), q, k_cache, v_cache, seq_lens, out, lse, workspace,
+                                     _raw_stream(stream)))
+        if st is not None:
+            return _check(st, "compkv_dense_decode")
     cache, _, _, qs = _shapes(dims)
     bf, f32 = torch.bfloat16, torch.float32
     ws, ws_bytes = _ws(workspace)
@@ -412,7 +423,7 @@ def compkv_dense_decode(dims, scale, q, k_cache, v_cache, seq_lens, out, lse=Non
 def compkv_decode_step(dims, params: CompkvSelectParams, q, k_cache, v_cache, k_new, v_new, seq_lens, kmean,
                        dvar, vmean, sel, n_sel, blk_logit, scores, out, lse=None, workspace=None, stream=None):
     """One fused decode step; seq_lens are the lengths after the new token (k_new/v_new may be None)."""
-    if (k_new is None) == (v_new is None):
+    if (k_new is None) == (v_new is None) and isinstance(params, CompkvSelectParams):
         st = _call(_STEP, dims, params.budget_blocks, (
             ctypes.addressof(params), q, k_cache, v_cache, k_new, v_new, seq_lens, kmean, dvar, vmean, sel, n_sel,
             blk_logit, scores, out, lse, workspace, _raw_stream(stream)))
@@ -441,7 +452,7 @@ def compkv_decode_step_noalloc(dims, params: CompkvSelectParams, q, k_cache, v_c
                                kmean, dvar, vmean, sel, n_sel, blk_logit, scores, out, lse=None, stream=None):
     """compkv_decode_step without a workspace: the library's fixed per-GPU scratch is used instead
     (nothing is allocated; overlapping calls on one GPU race)."""
-    if (k_new is None) == (v_new is None):
+    if (k_new is None) == (v_new is None) and isinstance(params, CompkvSelectParams):
         st = _call(_STEP_NOALLOC, dims, params.budget_blocks, (
             ctypes.addressof(params), q, k_cache, v_cache, k_new, v_new, seq_lens, kmean, dvar, vmean, sel, n_sel,
             blk_logit, scores, out, lse, _raw_stream(stream)))

@@ -53,6 +53,45 @@ def test_specs_follow_the_values_of_dims():
     assert bytes(d) != bytes(P.make_dims(1, 8, 2, 128, 16, 4, 4096))
 
 
+_SP = P.CompkvSelectParams(4, 1, 2, 0.1)
+
+
+@pytest.mark.parametrize("call,n", [(P.compkv_build_stats, 6), (P.compkv_append_stats, 8), (P.compkv_score_select, 9),
+                                    (P.compkv_sparse_decode, 10), (P.compkv_dense_decode, 7), (P.compkv_decode_step, 15),
+                                    (P.compkv_decode_step_noalloc, 15)])
+@pytest.mark.parametrize("dims", ["good", "no_kv_heads", "no_blocks", None])
+@pytest.mark.parametrize("head", [_SP, None, 0.5, "x"])
+def test_wrong_calls_fail_as_without_the_native_path(monkeypatch, call, n, dims, head):
+    """Dims that form no shapes, dims and parameters that are none, tensors on the CPU: the same error, type and
+    words, as from the checks in Python alone."""
+    if isinstance(dims, str):
+        d = P.make_dims(1, 8, 2, 128, 16, 4, 4096)
+        if dims == "no_kv_heads":
+            d.n_kv_heads = 0
+        if dims == "no_blocks":
+            d.block_size = 0
+    else:
+        d = dims
+    takes_head = call not in (P.compkv_build_stats, P.compkv_append_stats)
+    for x in (torch.zeros(1, 2, 4), None):
+        args = (d, head, *[x] * n) if takes_head else (d, *[x] * n)
+        got = []
+        for native in (True, False):
+            with monkeypatch.context() as m:
+                if not native:
+                    m.setattr(B, "_call", lambda *a: None)
+                with pytest.raises(Exception) as e:
+                    call(*args)
+                got.append((e.type, str(e.value)))
+        assert got[0] == got[1]
+
+
+def test_only_an_integer_is_a_stream():
+    """A stream that is no handle is left to the checks in Python, which refuse it."""
+    assert B._raw_stream(7) == 7
+    assert B._raw_stream(0.0) is None and B._raw_stream("0") is None
+
+
 @pytest.mark.gpu
 def test_wrong_tensors_are_named():
     """Each wrong argument of a step is refused with the binding's own message, and nothing is launched."""
@@ -72,4 +111,6 @@ def test_wrong_tensors_are_named():
     for name, (value, message) in bad.items():
         with pytest.raises(P.CompkvError, match=message):
             P.compkv_decode_step(d, prm, **{**args, name: value})
+    with pytest.raises(ctypes.ArgumentError):
+        P.compkv_decode_step(d, prm, **args, stream=0.0)
     torch.cuda.synchronize()
