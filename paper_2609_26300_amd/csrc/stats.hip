@@ -199,15 +199,20 @@ void launch_build_wave(const Geom& g, const StatsArgs& a, int most, hipStream_t 
 }
 
 // One wave per block up to 64 rows at d = 128 (128 at d = 64), by the load steps the block needs; larger
-// blocks are shared by a workgroup's four waves. (Against the workgroup form: blocks of 64 at d = 128 436 ->
-// 413 us for 2.2 GB.)
+// blocks are shared by a workgroup's four waves. So are blocks of more than 32 rows (64 at d = 64) while they are too
+// few to give every wave of a round one: a wave then takes 16 rows in turn where four waves share them. Measured, us with the
+// workgroup / the wave form: blocks of 64, d = 128: 64 blocks 4.9 / 8.2, 512 6.6 / 9.3, 1024 9.3 / 11.3, 2048 (a block for
+// every wave) 18.4 / 16.4, 8192 58.0 / 54.1, 32768 217 / 204; blocks of 96, d = 64: 1024 8.2 / 10.7, 2048 17.2 / 16.3,
+// 16384 90 / 77.
 template <int D>
 void launch_build_d(const Geom& g, const StatsArgs& a, hipStream_t s) {
     const int small = D == 64 ? (g.B <= 16 ? 5 : 3) : 2;
     if (g.B <= wave_stats_max_rows<D>(1)) return launch_build_wave<D, 1, 1>(g, a, small, s);
     if (g.B <= wave_stats_max_rows<D>(2)) return launch_build_wave<D, 2, 2>(g, a, 2, s);
-    if (g.B <= wave_stats_max_rows<D>(4)) return launch_build_wave<D, 4, 2>(g, a, 2, s);
     const long long total = (long long)g.xmax() * g.units();
+    if (g.B <= wave_stats_max_rows<D>(4) &&
+        total >= (long long)resident_slots<build_stats_wave_kernel<D, 4, 2>>(kThreads, 2) * (kThreads / 64))
+        return launch_build_wave<D, 4, 2>(g, a, 2, s);
     const long long slots = resident_slots<build_stats_kernel<D>>();  // one resident round, grid-stride
     build_stats_kernel<D><<<dim3((unsigned)(total < slots ? total : slots)), kThreads, 0, s>>>(g, a);
 }

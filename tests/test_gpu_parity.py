@@ -300,3 +300,36 @@ def test_build_non_finite_rows(d, B, r):
                     got = got[b, :, x].cpu().numpy()
                     assert np.array_equal(np.isnan(got), np.isnan(want)) and np.array_equal(np.isposinf(got), np.isposinf(want))
                     assert np.array_equal(np.isneginf(got), np.isneginf(want))
+
+
+# enough blocks of more than 32 rows (d = 64: 64) for the wave build to take them too (at least one for each of its
+# waves, two workgroups of four per compute unit): against the oracle, and bit for bit against the append, also with
+# infinities in the first rows of partly filled blocks
+@pytest.mark.parametrize("d,B,r", [(128, 33, 4), (128, 64, 128), (64, 65, 1), (64, 128, 8)])
+def test_build_many_large_blocks(d, B, r):
+    import paper_2609_26300_amd as P
+
+    units = 2 * torch.cuda.get_device_properties(0).multi_processor_count // 4
+    lens = [17 * B - 1 - (7 * i) % (2 * B) for i in range(units // 2)]
+    c = Case(TINY.with_(batch=units // 2, head_dim=d, block_size=B, context=17 * B, n_var_groups=r, budget_blocks=2, seed=74),
+             seq_lens=lens, max_seq_len=17 * B)
+    assert c.dims.n_kv_heads == 2 and units * c.dims.xmax >= 8 * torch.cuda.get_device_properties(0).multi_processor_count
+    s = c.build_stats()
+    c.check_stats(s.kmean, s.dvar, s.vmean)
+    before = (c.sl - 1).to(torch.int32)
+    for planted in (False, True):
+        if planted:
+            for b in range(0, units // 2, 3):
+                row = (lens[b] - 1) // B * B
+                c.K[b, 0, row, b % d], c.V[b, 1, row, (5 * b) % d] = float("inf"), float("-inf")
+            s = c.build_stats()
+        kn = torch.stack([c.K[b, :, n - 1] for b, n in enumerate(lens)]).contiguous()
+        vn = torch.stack([c.V[b, :, n - 1] for b, n in enumerate(lens)]).contiguous()
+        a = P.alloc_summaries(c.dims)
+        P.compkv_build_stats(c.dims, c.K, c.V, before, a.kmean, a.dvar, a.vmean)
+        P.compkv_append_stats(c.dims, c.K, c.V, kn, vn, before, a.kmean, a.dvar, a.vmean)
+        torch.cuda.synchronize()
+        for k in ("kmean", "dvar", "vmean"):
+            x, y = (torch.nan_to_num(getattr(t, k), nan=7e37, posinf=8e37, neginf=9e37) for t in (a, s))
+            assert torch.equal(x, y), k
+            assert bool((x >= 7e37).any()) == planted
