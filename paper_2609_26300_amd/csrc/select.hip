@@ -192,13 +192,15 @@ __device__ void score_tail(const Geom& geo, const ScoreArgs& a, int u, TailShare
 // PMAX = bpc / 32: block slots per thread (the chunk is 32 PMAX blocks). Phase-trace slots: 0 start,
 // 1 role (1 chunk, 2 last block), 2 query in LDS, 3 first slot computed, 4 every slot computed,
 // 6 stores begin, 15 end.
-// kWide (more than eight variance groups): a slot's variances past the lane's first are requested with its
-// mean key too, all of them at once. (In a loop of dependent loads after the keys, 16 units of 1024 blocks
-// with a variance per coordinate, 17 MB, took 11.0 us; so 6.9.) The registers this takes stay out of the
-// narrow kernel, where they would cost a fifth of the resident workgroups.
-template <int D, int G, bool kStep, int PMAX, bool kWide>
+// RV: variances per lane and block that a slot may hold, 1 (up to eight variance groups), 4 (up to 32) or D / 8. With
+// more than one, a slot's variances past the lane's first are requested with its mean key too, all of them at
+// once. (In a loop of dependent loads after the keys, 16 units of 1024 blocks with a variance per coordinate, 17 MB,
+// took 11.0 us; so 6.9.) The registers this takes stay out of the kernels of fewer groups, where they would cost
+// resident workgroups: with D / 8 also for 16 and 32 groups, 64 units of 2048 blocks (G = 8, d = 128) took 67.4 us for the
+// two calls at r = 16 against 63.7 so (64.8 with the loop), 64.9 against 67.6 at r = 32. (A branch around the loads past
+// the last group costs 1 to 7%: they repeat the last group instead.)
+template <int D, int G, bool kStep, int PMAX, int RV>
 __global__ __launch_bounds__(kThreads) void score_chunks_kernel(Geom geo, ScoreArgs a) {
-    constexpr int RV = kWide ? D / 8 : 1;  // variances per lane and block
     constexpr int NB = chunk_slots<PMAX>();
     static_assert(NB % 64 == 0 && NB >= 32 * PMAX, "per-block rows must cover the chunk and whole waves");
     __shared__ ChunkLds<D, G, kStep, NB> lds;
@@ -304,7 +306,7 @@ __global__ __launch_bounds__(kThreads) void score_chunks_kernel(Geom geo, ScoreA
             // the rounded product, not fused into the sum over the lanes: the other launch shapes' bits
             __asm__("" : "+v"(v[g]));
         }
-        if constexpr (kWide) {
+        if constexpr (RV > 1) {
 #pragma unroll
             for (int j = 1; j < RV; ++j) {
                 if (8 * j >= geo.r) break;  // workgroup-uniform (r is a multiple of eight here)
@@ -663,28 +665,30 @@ __global__ __launch_bounds__(kFinThreads) void unit_select_kernel(Geom geo, Scor
     select_radix(sc, sh);
 }
 
-template <int D, int G, bool kStep, int PMAX, bool kWide>
+template <int D, int G, bool kStep, int PMAX, int RV>
 void launch_chunks_p(const Geom& g, ScoreArgs a, hipStream_t s) {
     const int grid = (a.nchunks + 1) * g.units();
-    a.tail_first = grid <= resident_slots<score_chunks_kernel<D, G, kStep, PMAX, kWide>>();
-    score_chunks_kernel<D, G, kStep, PMAX, kWide><<<dim3(grid), kThreads, 0, s>>>(g, a);
+    a.tail_first = grid <= resident_slots<score_chunks_kernel<D, G, kStep, PMAX, RV>>();
+    score_chunks_kernel<D, G, kStep, PMAX, RV><<<dim3(grid), kThreads, 0, s>>>(g, a);
 }
 
-template <int D, int G, bool kStep, bool kWide>
-void launch_chunks_w(const Geom& g, const ScoreArgs& a, hipStream_t s) {
+template <int D, int G, bool kStep, int RV>
+void launch_chunks_r(const Geom& g, const ScoreArgs& a, hipStream_t s) {
     switch (a.bpc / 32) {
-        case 1: launch_chunks_p<D, G, kStep, 1, kWide>(g, a, s); break;
-        case 2: launch_chunks_p<D, G, kStep, 2, kWide>(g, a, s); break;
-        default: launch_chunks_p<D, G, kStep, 4, kWide>(g, a, s); break;
+        case 1: launch_chunks_p<D, G, kStep, 1, RV>(g, a, s); break;
+        case 2: launch_chunks_p<D, G, kStep, 2, RV>(g, a, s); break;
+        default: launch_chunks_p<D, G, kStep, 4, RV>(g, a, s); break;
     }
 }
 
 template <int D, int G, bool kStep>
 void launch_chunks(const Geom& g, const ScoreArgs& a, hipStream_t s) {
-    if (g.r > 8)
-        launch_chunks_w<D, G, kStep, true>(g, a, s);
+    if (g.r <= 8)
+        launch_chunks_r<D, G, kStep, 1>(g, a, s);
+    else if (g.r <= 32)
+        launch_chunks_r<D, G, kStep, 4>(g, a, s);
     else
-        launch_chunks_w<D, G, kStep, false>(g, a, s);
+        launch_chunks_r<D, G, kStep, D / 8>(g, a, s);
 }
 
 template <int D, int G>
