@@ -54,6 +54,6 @@ def test_scoring_of_few_groups_keeps_its_residency(kernels):
     """The chunk scoring of up to 32 variance groups holds at least four waves per SIMD (128 registers), as without the
     variances in flight; only the kernel of more groups takes more."""
     few = [k[".vgpr_count"] for k in kernels
-           if "score_chunks_kernelILi" in k[".name"] and k[".name"].split("EEv")[0].endswith(("ELi1", "ELi4"))]
+           if "score_chunks_kernelILi" in k[".name"] and k[".name"].split("EEEv")[0].endswith(("ELi1", "ELi4"))]
     assert len(few) == 2 * 2 * 4 * 2 * 3  # (groups kept per lane, head sizes, query heads, step or call, slots)
     assert max(few) <= 128
