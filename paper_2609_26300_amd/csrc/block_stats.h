@@ -7,14 +7,19 @@
 
 namespace compkv {
 
+// A block's summary in LDS: all that a workgroup needs that forms none itself.
 template <int D>
-struct BlockStatsLds {
-    // partial sums of each row group of each wave (4 waves of 64 / (d/8) groups): key, value; later the
-    // squared deviations in the key's place
-    alignas(16) float part[4][64 / (D / 8)][2][D];
+struct BlockMeansLds {
     alignas(16) float km[D];
     alignas(16) float vm[D];
     float dv[D];
+};
+
+template <int D>
+struct BlockStatsLds : BlockMeansLds<D> {
+    // partial sums of each row group of each wave (4 waves of 64 / (d/8) groups): key, value; later the
+    // squared deviations in the key's place
+    alignas(16) float part[4][64 / (D / 8)][2][D];
 };
 
 // Summary of one block of nb >= 1 rows (row j at Kb + j*D; row new_j, if >= 0, is read from k_new /

@@ -72,9 +72,11 @@ struct CompShared {
 };
 struct NoComp {};
 
-template <int D, int G>
+template <int D, int G, bool kStep>
 struct TailShared {
-    BlockStatsLds<D> bs;  // the last block's summary (km, vm, dv)
+    // the last block's summary (km, vm, dv); the scoring call forms none, so its workgroups go without the 16 KB of
+    // partial sums (19 to 26 KB a workgroup with them, 7 to 16 without: 8 waves per SIMD again instead of 6 at G = 8)
+    std::conditional_t<kStep, BlockStatsLds<D>, BlockMeansLds<D>> bs;
     float q[G][D];
     float Qv[G][D];
     float z[G], v[G];
@@ -87,12 +89,12 @@ union ChunkLds {
         ChunkShared<D, G, NB> sh;
         std::conditional_t<kStep, CompShared<D, G, NB>, NoComp> st;
     } c;
-    TailShared<D, G> t;
+    TailShared<D, G, kStep> t;
 };
 
 // The extra workgroup of unit u: the last block X - 1 (refreshed first when the step appends).
 template <int D, int G, bool kStep>
-__device__ void score_tail(const Geom& geo, const ScoreArgs& a, int u, TailShared<D, G>& ts) {
+__device__ void score_tail(const Geom& geo, const ScoreArgs& a, int u, TailShared<D, G, kStep>& ts) {
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int bseq = u / geo.hkv, h = u % geo.hkv;
     const int nc = a.nchunks;
@@ -128,14 +130,16 @@ __device__ void score_tail(const Geom& geo, const ScoreArgs& a, int u, TailShare
     // is scored over max_seq_len tokens from its stored summaries, as in the separate calls
     const bool append = kStep && a.k_new && n_raw <= geo.max_seq;
     if (append) {  // the summary reads row n - 1 from k_new / v_new; the cache row is stored at the end
-        const size_t row0 = (size_t)block_row0(geo, u, b);
-        const BlockSrc src{a.Kc + row0 * D, a.Vc + row0 * D, a.k_new + (size_t)u * D, a.v_new + (size_t)u * D, nb,
-                           nb - 1};
-        BlockRows rows;
-        load_block_rows<D>(src, 0, rows);
-        store_query<D, G>(qp, a.scale, geo.r, geo.layout, ts.q, ts.Qv);  // while the rows are in flight
-        block_stats_from<D>(src, rows, geo.r, geo.layout, a.kmean_w + blk * D, a.dvar_w + blk * geo.r,
-                            a.vmean + blk * D, ts.bs);  // (its barriers also publish ts.q / ts.Qv)
+        if constexpr (kStep) {
+            const size_t row0 = (size_t)block_row0(geo, u, b);
+            const BlockSrc src{a.Kc + row0 * D, a.Vc + row0 * D, a.k_new + (size_t)u * D, a.v_new + (size_t)u * D, nb,
+                               nb - 1};
+            BlockRows rows;
+            load_block_rows<D>(src, 0, rows);
+            store_query<D, G>(qp, a.scale, geo.r, geo.layout, ts.q, ts.Qv);  // while the rows are in flight
+            block_stats_from<D>(src, rows, geo.r, geo.layout, a.kmean_w + blk * D, a.dvar_w + blk * geo.r,
+                                a.vmean + blk * D, ts.bs);  // (its barriers also publish ts.q / ts.Qv)
+        }
     } else {
         for (int i = tid; i < D; i += kThreads) {
             ts.bs.km[i] = a.kmean[blk * D + i];

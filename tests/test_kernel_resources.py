@@ -57,3 +57,11 @@ def test_scoring_of_few_groups_keeps_its_residency(kernels):
            if "score_chunks_kernelILi" in k[".name"] and k[".name"].split("EEEv")[0].endswith(("ELi1", "ELi4"))]
     assert len(few) == 2 * 2 * 4 * 2 * 3  # (groups kept per lane, head sizes, query heads, step or call, slots)
     assert max(few) <= 128
+
+
+def test_scoring_call_keeps_its_lds(kernels):
+    """The scoring call's chunk workgroups (no append) hold no partial sums of a summary: eight fit the 160 KB of a
+    compute unit."""
+    lds = [k[".group_segment_fixed_size"] for k in kernels
+           if "score_chunks_kernelILi" in k[".name"] and "ELb0E" in k[".name"]]
+    assert lds and max(lds) * 8 <= 160 * 1024
