@@ -285,8 +285,9 @@ SxShape sx_shape(const Geom& g, int nchunks, int K) {
     //    2 units of 4K 19.3 / 17.4, 32 units of 4K 22.9 / 20.8, 96 units of 16K 54.8 / 47.2, 64 units of 64K
     //    55.3 / 54.3). With eight heads per unit up to 32 units of 1024 blocks (16 units of 16K 26.4 / 24.5,
     //    but 64 units of 64K, where its selection holds up the stream, 45.5 / 47.3).
-    // At more blocks the 1024-thread form's selection is faster (8 units of 128K 28.1 / 31.7).
-    const bool many = 2 * g.units() > resident && (g.G != 8 || xmax <= 2048);
+    // At more blocks the 1024-thread form's selection is faster (8 units of 128K 28.1 / 31.7), and more than half
+    // as many units as CUs have no room for the four workgroups that their mean values then need.
+    const bool many = 2 * g.units() > resident && xmax <= 2048;
     const bool brief = g.G == 8 ? xmax <= 1024 && g.units() <= 32 : xmax <= 2048;
     const bool small = many || brief;
     const int wt = small ? 512 : 1024;

@@ -137,7 +137,8 @@ constexpr uint32_t kPosted = 0x80000000u;  // mailbox value of id b: b ^ kPosted
 constexpr uint32_t kSelFailed = 1u;        // selection word: a worker's wait timed out
 constexpr int kSelSpinLimit = 1 << 17;     // polls of a wait (each a memory round trip): well over 50 ms
 
-// FT: threads, 1024 (one workgroup per CU) or 512 (two per CU: many units, chosen by the host); KPT: keys per thread of the selection (xmax <= KPT FT); kLogits: a.logit_terms
+// FT: threads, 1024 (one workgroup per CU) or 512 (two per CU: short units or many of them, chosen by the host, at
+// most 2048 blocks); KPT: keys per thread of the selection (xmax <= KPT FT); kLogits: a.logit_terms
 template <int D, int G, int FT, int KPT, bool kLogits = false>
 __global__ __launch_bounds__(FT) void select_work_kernel(Geom geo, ScoreArgs a, DecodeArgs d, int P) {
     constexpr int NW = FT / 64;
@@ -222,7 +223,7 @@ template <int D, int G>
 hipError_t launch_sx(const Geom& g, const ScoreArgs& a, const DecodeArgs& d, int items, hipStream_t s) {
     const dim3 grid((items + d.n_comp) * g.units());
     const size_t dyn = finalize_dyn_lds(g, a);
-    if constexpr (G >= 4) {
+    if constexpr (G == 8) {
         if (a.logit_terms) {  // (at most 4096 blocks: checked by the launcher)
             if (g.xmax() <= kSxThreads)
                 select_exact_kernel<D, G, kSxThreads, 1, true><<<grid, kSxThreads, dyn, s>>>(g, a, d, items);
@@ -245,26 +246,28 @@ template <int D, int G, int FT>
 hipError_t launch_work(const Geom& g, const ScoreArgs& a, const DecodeArgs& d, int P, hipStream_t s) {
     const dim3 grid(P * g.units());
     const size_t dyn = finalize_dyn_lds(g, a);
-    if constexpr (G >= 4) {
+    const int xmax = g.xmax();  // (FT = 512: at most 4 FT blocks, checked by the launcher)
+    constexpr int K2 = FT < 1024 ? 2 : 4;
+    if constexpr (G == 8) {
         if (a.logit_terms) {  // (at most 4 FT blocks: checked by the launcher)
-            if (g.xmax() <= FT)
+            if (xmax <= FT)
                 select_work_kernel<D, G, FT, 1, true><<<grid, FT, dyn, s>>>(g, a, d, P);
-            else if (FT < 1024 && g.xmax() <= 2 * FT)
-                select_work_kernel<D, G, FT, FT < 1024 ? 2 : 4, true><<<grid, FT, dyn, s>>>(g, a, d, P);
+            else if (xmax <= K2 * FT)
+                select_work_kernel<D, G, FT, K2, true><<<grid, FT, dyn, s>>>(g, a, d, P);
             else
                 select_work_kernel<D, G, FT, 4, true><<<grid, FT, dyn, s>>>(g, a, d, P);
             return hipGetLastError();
         }
     }
     // keys per thread for the unit's blocks: fewer loads and keys where the blocks are few
-    if (g.xmax() <= FT)
+    if (xmax <= FT)
         select_work_kernel<D, G, FT, 1><<<grid, FT, dyn, s>>>(g, a, d, P);
-    else if (FT < 1024 && g.xmax() <= 2 * FT)
-        select_work_kernel<D, G, FT, FT < 1024 ? 2 : 4><<<grid, FT, dyn, s>>>(g, a, d, P);
-    else if (g.xmax() <= 4 * FT)
+    else if (xmax <= K2 * FT)
+        select_work_kernel<D, G, FT, K2><<<grid, FT, dyn, s>>>(g, a, d, P);
+    else if (FT < 1024 || xmax <= 4 * FT)
         select_work_kernel<D, G, FT, 4><<<grid, FT, dyn, s>>>(g, a, d, P);
-    else
-        select_work_kernel<D, G, FT, 8192 / FT><<<grid, FT, dyn, s>>>(g, a, d, P);
+    else if constexpr (FT == 1024)
+        select_work_kernel<D, G, FT, 8><<<grid, FT, dyn, s>>>(g, a, d, P);
     return hipGetLastError();
 }
 
@@ -315,7 +318,7 @@ int sx_slots(size_t dyn, int threads) {
         if (known[i].dev == dev && known[i].threads == threads && known[i].dyn == dyn) return known[i].slots;
     if ((threads == kSxThreads
              ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, select_work_kernel<D, G, 1024, 8>, 1024, dyn)
-             : hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, select_work_kernel<D, G, 512, 16>, 512, dyn)) !=
+             : hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, select_work_kernel<D, G, 512, 4>, 512, dyn)) !=
             hipSuccess ||
         hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
         return 0;
@@ -352,13 +355,14 @@ hipError_t launch_select_work(const Geom& g, ScoreArgs a, const DecodeArgs& d, i
     a.keys_in_lds = 1;
     if (!logit_terms_ok(g, a)) return hipErrorInvalidValue;
     const int keff = std::max(1, std::min(a.K, g.xmax()));
-    if (P < 2 || a.bpc < 1 || (a.bpc & (a.bpc - 1)) != 0 || g.xmax() > kFinThreads * kKeysPerThread || a.K > kSelLdsMax || d.eb < 1 || d.eb > kMaxEb ||
-        (long long)P * d.eb < keff || finalize_dyn_lds(g, a) > kDynBudget || !d.arrive || !d.sel_word || !d.mailbox ||
+    if (P < 2 || a.bpc < 1 || (a.bpc & (a.bpc - 1)) != 0 || g.xmax() > kFinThreads * kKeysPerThread || a.K > kSelLdsMax ||
+        d.eb < 1 || d.eb > kMaxEb || (long long)P * d.eb < keff || finalize_dyn_lds(g, a) > kDynBudget || !d.arrive ||
+        !d.sel_word || !d.mailbox ||
         (d.n_comp != 0 && (d.n_comp != P - 1 || d.cb < 1 || d.cb > kStepCbMax || (long long)d.n_comp * d.cb < g.xmax())) ||
         d.part_base != 0 || d.part_count != P || d.part_count * g.G > kMergeMaxTerms)
         return hipErrorInvalidValue;
     if (threads == 512) {
-        if (a.logit_terms && g.xmax() > 4 * threads) return hipErrorInvalidValue;
+        if (g.xmax() > 4 * threads) return hipErrorInvalidValue;
         return g.D == 128 ? work_g<128, 512>(g, a, d, P, s) : work_g<64, 512>(g, a, d, P, s);
     }
     if (threads != kSxThreads) return hipErrorInvalidValue;

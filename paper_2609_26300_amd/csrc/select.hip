@@ -711,7 +711,7 @@ hipError_t launch_pair(const Geom& g, const ScoreArgs& a, hipStream_t s) {
         launch_chunks<D, G, false>(g, a, s);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || a.chunks_only) return e;
-    if constexpr (G >= 4) {
+    if constexpr (G == 8) {
         if (a.logit_terms) {
             select_finalize_kernel<G, true><<<dim3(g.units()), kFinThreads, finalize_dyn_lds(g, a), s>>>(g, a);
             return hipGetLastError();
@@ -738,7 +738,7 @@ int select_max_bpc() { return kBpcMax; }
 
 // the selection's logit-terms input (ScoreArgs::logit_terms) within its limits
 bool logit_terms_ok(const Geom& g, const ScoreArgs& a) {
-    return !a.logit_terms || (g.r == 4 && g.G >= 4 && g.G <= 8 && g.xmax() <= 4 * kFinThreads && a.zlog && a.ws_qv);
+    return !a.logit_terms || (g.r == 4 && g.G == 8 && g.xmax() <= 4 * kFinThreads && a.zlog && a.ws_qv);
 }
 
 int select_one_group_terms() { return kUnitTerms; }

@@ -416,18 +416,17 @@ __device__ void select_radix(const SelectCtx& c, FinalShared& sh) {
 // or LDS). dyn: [np][G] partial maxima, then factors; [np][G] sums; [xmax] key bits (keys_in_lds).
 // kCoh: the partials and terms were written by other workgroups of the same launch (device-coherent
 // loads; the values of blocks past the unit's, loaded only to keep the loads in flight fixed, go unused).
-// FT threads holding up to KPT keys each (the terms of the first eight requested up front, the rest
-// once the normalizers are formed).
-// kLogits (a.logit_terms, G >= 4, r = 4, at most 4096 blocks): block b's terms are formed here from
+// FT threads holding up to KPT keys each.
+// kLogits (a.logit_terms, G = 8, r = 4, at most 4096 blocks): block b's terms are formed here from
 // zbar (a.zlog), its variances (dvar) and the query's group sums (a.ws_qv): sig2_{g,b} = sum_t
 // s^2 Q_{g,t} D_{b,t}, a_{g,b} = log|b| + zbar_{g,b} + half * sig2_{g,b}, and S_b = sum_g
 // exp(a_{g,b} - lse_g) * term(sig2_{g,b}), with lse_g from the chunk partials as above.
 template <int G, bool kCoh = false, int FT = kFinThreads, int KPT = kKeysPerThread, bool kLogits = false>
 __device__ void finalize_select(const Geom& geo, const ScoreArgs& a, int u, FinalShared& sh, float* dyn,
                                 int32_t* sel_out, int32_t* nsel_out, bool write_scores) {
-    static_assert(!kLogits || (G >= 4 && G <= 8 && !kCoh && KPT <= 4), "logit terms: four to eight heads, one "
-                                                                         "launch apart, at most 4096 blocks");
-    constexpr int KB = KPT < 8 ? KPT : 8;
+    static_assert(KPT <= 8, "the terms of every key are requested up front");
+    static_assert(!kLogits || (G == 8 && !kCoh && KPT <= 4), "logit terms: eight heads, one launch apart, at most "
+                                                              "4096 blocks");
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int bseq = u / geo.hkv;
     const int xmax = geo.xmax();
@@ -451,10 +450,10 @@ __device__ void finalize_select(const Geom& geo, const ScoreArgs& a, int u, Fina
     if constexpr (kLogits) qv = a.ws_qv[(size_t)u * G * 4 + (tid < G * 4 ? tid : 0)];
     __asm__ volatile("" ::: "memory");
     // score terms (or, kLogits, zbar of each head and the block's four variances)
-    float w[KB][G];
-    float4 dvk[kLogits ? KB : 1];
+    float w[KPT][G];
+    float4 dvk[kLogits ? KPT : 1];
 #pragma unroll
-    for (int k = 0; k < KB; ++k) {  // ids past xmax load block 0, unused
+    for (int k = 0; k < KPT; ++k) {  // ids past xmax load block 0, unused
         const int b = tid + k * FT;
         const int bb = b < xmax ? b : 0;
         if constexpr (kLogits) {
@@ -552,22 +551,7 @@ __device__ void finalize_select(const Geom& geo, const ScoreArgs& a, int u, Fina
             }
         };
 #pragma unroll
-        for (int k = 0; k < KB; ++k) key(k, w[k]);
-        if constexpr (KPT > KB) {
-            float w2[KPT - KB][G];
-#pragma unroll
-            for (int k = KB; k < KPT; ++k) {
-                if (k * FT >= xmax) {  // (workgroup-uniform)
-#pragma unroll
-                    for (int g = 0; g < G; ++g) w2[k - KB][g] = 0.0f;
-                } else {
-                    const int b = tid + k * FT;
-                    load_terms<G, kCoh>(wu, b < xmax ? b : 0, w2[k - KB]);
-                }
-            }
-#pragma unroll
-            for (int k = KB; k < KPT; ++k) key(k, w2[k - KB]);
-        }
+        for (int k = 0; k < KPT; ++k) key(k, w[k]);
         COMPKV_MARK(a.trace, 3);  // normalizers and keys formed
         if (select_fast<KPT, FT>(sc, ck, mx, sh)) return;
     } else {
@@ -693,10 +677,9 @@ __device__ void merge_unit(const Geom& geo, const DecodeArgs& d, int u, Lds& L, 
     constexpr int SPLIT = GD >= FT ? 1 : FT / GD;
     static_assert(SPLIT == 1 || SPLIT * GD <= (int)(sizeof(L.cw) / sizeof(float)), "split sums fit in LDS");
     if (d.part_count <= 64) {  // (workgroup-uniform)
-        constexpr int SP = G * D >= FT ? 1 : FT / (G * D);
-        if (d.part_count <= 4 * SP)
+        if (d.part_count <= 4 * SPLIT)
             merge_unit_lanes<D, G, Lds, FT, 4>(geo, d, u, L, poison);
-        else if (d.part_count <= 12 * SP)
+        else if (d.part_count <= 12 * SPLIT)
             merge_unit_lanes<D, G, Lds, FT, 12>(geo, d, u, L, poison);
         else
             merge_unit_lanes<D, G, Lds, FT, 20>(geo, d, u, L, poison);

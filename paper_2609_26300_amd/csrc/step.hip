@@ -372,7 +372,7 @@ __device__ void step_select(const Geom& geo, const ScoreArgs& a, const DecodeArg
     const int tid = threadIdx.x;
     SelExactLdsT<D, G, kStepCbMax>& S = L.u.sx;
     bool done = false;
-    if constexpr (G >= 4) {
+    if constexpr (G == 8) {
         if (a.logit_terms) {  // (workgroup-uniform)
             finalize_select<G, false, kFinThreads, 4, true>(geo, a, u, S.u.fin, dyn, S.sel, &S.nsel, true);
             done = true;
