@@ -114,3 +114,16 @@ def test_wrong_tensors_are_named():
     with pytest.raises(ctypes.ArgumentError):
         P.compkv_decode_step(d, prm, **args, stream=0.0)
     torch.cuda.synchronize()
+
+
+def test_either_library_comes_with_the_call_path(monkeypatch, tmp_path):
+    """Both builds make _host.so: the binding enters the trace library through it too."""
+    from paper_2609_26300_amd import build as lib_build
+
+    for name in ("BUILD", "LIB", "TRACE_LIB", "HOST_LIB"):
+        monkeypatch.setattr(lib_build, name, str(tmp_path / name))
+    for trace in (False, True):
+        made = []
+        monkeypatch.setattr(lib_build, "_run", lambda cmd, verbose: (made.append(cmd), open(cmd[cmd.index("-o") + 1], "w").close()))
+        lib_build.build(trace=trace)
+        assert any(c[0] == "g++" and any(a.endswith("host.cpp") for a in c) for c in made), trace
