@@ -286,6 +286,13 @@ size_t compkv_decode_step_noalloc_limit(void);
  */
 int compkv_phase_trace_set(void* chunk_records, void* fused_records);
 
+/*
+ * Polls that a workgroup of the fused selection/exact launch waits for its unit's selected ids before it makes the
+ * selection itself (trace build, for tests of that: with 0 it does so unless the ids are there already; negative: the
+ * usual number). Returns COMPKV_OK, or COMPKV_EUNSUPPORTED from a library built without the trace.
+ */
+int compkv_select_polls_set(int polls);
+
 /* The launch shape compkv_decode_step takes for these dims and params on the current device:
  * COMPKV_SELECT_ONE_GROUP, COMPKV_SELECT_CHUNKED or COMPKV_SELECT_CHUNKED_EXACT (params->select_path
  * resolved), or a negative status (invalid dims or path). Enqueues nothing. */

@@ -117,6 +117,8 @@ def library():
         L.compkv_decode_step_path.argtypes = [dp, ctypes.POINTER(CompkvSelectParams)]
         L.compkv_phase_trace_set.argtypes = [_vp, _vp]
         L.compkv_phase_trace_set.restype = ctypes.c_int
+        L.compkv_select_polls_set.argtypes = [_i32]
+        L.compkv_select_polls_set.restype = ctypes.c_int
         L.compkv_host_cache_pointer.argtypes = [_vp, ctypes.POINTER(ctypes.c_void_p)]
         L.compkv_host_cache_pointer.restype = ctypes.c_int
         L.compkv_workspace_bytes.argtypes = [dp, _i32, _i32]
@@ -492,6 +494,11 @@ def compkv_phase_trace_set(chunk_records=None, fused_records=None) -> None:
             raise CompkvError(f"{name} must be a contiguous int64 device tensor")
         ptrs.append(ctypes.c_void_p(t_.data_ptr()))
     _check(library().compkv_phase_trace_set(*ptrs), "compkv_phase_trace_set")
+
+
+def compkv_select_polls_set(polls: int) -> None:
+    """Trace build, for tests: polls of the fused launch's waits for selected ids (negative: the usual number)."""
+    _check(library().compkv_select_polls_set(int(polls)), "compkv_select_polls_set")
 
 
 def default_scale(head_dim: int) -> float:

@@ -158,6 +158,8 @@ size_t dense_ws(const Geom& g) {
 unsigned long long* g_trace_chunks = nullptr;
 unsigned long long* g_trace_fused = nullptr;
 
+int g_select_polls = -1;  // trace build: polls of the one-selector form's waits (negative: as many as usual)
+
 struct SxShape {  // the fused step's selection + exact launch (sx_shape below)
     int eb, n_exact;
     int cb, n_comp;  // its compensation workgroups: blocks each, workgroups per unit
@@ -192,12 +194,11 @@ int step_partials(const Geom& g, int K) {
                     sx.work ? sx.P : 0);
 }
 
-// fused step: the arrival counters of the fused selection/exact launch's in-launch merge and the
-// selection words of its one-selector form (one each per unit), then that form's mailbox of posted ids
-// ([units][K]), follow the partials
+// fused step: the arrival counters of the fused selection/exact launch's in-launch merge (one per unit), then
+// its one-selector form's mailbox of posted ids ([units][K]), follow the partials
 size_t step_ws(const Geom& g, int K) {
     return score_ws(g) + step_part_bytes(g, step_partials(g, K)) +
-           align_up((size_t)g.units() * (2 + (size_t)K) * sizeof(uint32_t));
+           align_up((size_t)g.units() * (1 + (size_t)K) * sizeof(uint32_t));
 }
 
 StreamShape stream_shape(const Geom& g, int K, bool mean);
@@ -795,8 +796,8 @@ int compkv_decode_step(const compkv_dims* dims, const compkv_select_params* para
         d.neg_pseudo = drop ? 0 : 1;
         d.sel_padded = 1;
         d.arrive = arrive;
-        d.sel_word = arrive + g.units();
-        d.mailbox = arrive + 2 * (size_t)g.units();
+        d.mailbox = arrive + g.units();
+        d.polls = g_select_polls < 0 ? compkv::select_poll_limit() : g_select_polls;
         d.timeouts = state;
         d.trace = g_trace_fused;
         a.trace = g_trace_fused;  // (the selection's marks, in the fused launch's records)
@@ -850,6 +851,16 @@ int compkv_phase_trace_set(void* chunk_records, void* fused_records) {
 #else
     (void)chunk_records;
     (void)fused_records;
+    return COMPKV_EUNSUPPORTED;
+#endif
+}
+
+int compkv_select_polls_set(int polls) {
+#ifdef COMPKV_PHASE_TRACE
+    g_select_polls = polls;
+    return COMPKV_OK;
+#else
+    (void)polls;
     return COMPKV_EUNSUPPORTED;
 #endif
 }

@@ -124,18 +124,22 @@ __global__ __launch_bounds__(FT) void select_exact_kernel(Geom geo, ScoreArgs a,
 // (id ^ kPosted, device-coherent; the chunk launch zeroed the mailbox, and no posted value is zero),
 // then attends exactly over the first eb ids. Worker w (1 .. P - 1) first streams its share of the
 // mean values (compensation blocks [(w - 1) cb, w cb)), requesting its slots [w eb, (w + 1) eb) of the
-// mailbox once the last mean values are in; a slot still zero is polled until posted (a bounded wait:
-// the selector started before any worker and never waits itself; past the bound the unit's outputs
-// become NaN and its timeout word counts it). Then it attends exactly over those ids, and its
-// compensation partial (kept in LDS) joins its exact partial: workgroup w stores partial w, and the
-// unit's last workgroup of P merges the P partials. The HBM streams from the start on every CU but the
+// mailbox once the last mean values are in; a slot still zero is polled until posted. Then it attends exactly over
+// those ids, and its compensation partial (kept in LDS) joins its exact partial: workgroup w stores partial w,
+// and the unit's last workgroup of P merges the P partials. The HBM streams from the start on every CU but the
 // selectors', and the selection runs once per unit.
+//
+// The wait depends on the selector having started, and nothing guarantees that it has: selectors come first in the
+// grid, and where the units fill whole rounds of eight a unit's workgroups queue on one XCD, its selector ahead; but
+// otherwise a worker may run on one XCD while its selector still queues on another, behind workgroups of another
+// stream that may themselves be waiting. So the wait is bounded (d.polls), and a worker that ends it without its ids
+// makes the selection itself (the same computation: the same ids): whatever else runs on the GPU and in whatever
+// order workgroups start, every workgroup ends and the results are the same. The unit's timeout word counts such waits.
 // Phase-trace slots (both forms of the fused launch): 0 start, 1 role (1 selects, 2 streams mean values
 // first), 2 the selection's loads in, 3 keys formed, 4 selected, 5 compensation weights formed, 6 mean
 // values weighed, 7 ids in hand (worker), 8 wave 0's tiles attended, 9 partial stored, 10 merges, 15 end.
 constexpr uint32_t kPosted = 0x80000000u;  // mailbox value of id b: b ^ kPosted (-1 gives 0x7FFFFFFF)
-constexpr uint32_t kSelFailed = 1u;        // selection word: a worker's wait timed out
-constexpr int kSelSpinLimit = 1 << 17;     // polls of a wait (each a memory round trip): well over 50 ms
+constexpr int kSelPollLimit = 1 << 14;     // polls of a wait (each a memory round trip): about 10 ms
 
 // FT: threads, 1024 (one workgroup per CU) or 512 (two per CU: short units or many of them, chosen by the host, at
 // most 2048 blocks); KPT: keys per thread of the selection (xmax <= KPT FT); kLogits: a.logit_terms
@@ -156,28 +160,18 @@ __global__ __launch_bounds__(FT) void select_work_kernel(Geom geo, ScoreArgs a, 
         xcd_unit_work((int)blockIdx.x - units, units, P - 1, u, w);
         ++w;
     }
-    uint32_t* word = d.sel_word + u;
     uint32_t* mbox = d.mailbox + (size_t)u * a.K;
     COMPKV_MARK_VALUE(d.trace, 1, w == 0 ? 1 : 2);
-    if (w == 0) {
-        finalize_select<G, false, FT, KPT, kLogits>(geo, a, u, L.u.fin, dyn, L.sel, &L.nsel, true);
-        __syncthreads();
-        COMPKV_MARK(d.trace, 4);  // selected
-        for (int k = tid; k < a.K; k += FT) {
-            const int32_t b = L.sel[k];
-            st_agent_u32(mbox + k, (uint32_t)b ^ kPosted);
-            a.sel[(size_t)u * a.K + k] = b;
-        }
-        if (tid == 0) a.n_sel[u] = L.nsel;
-        const int n = clamp_len(d.seq_lens[u / geo.hkv], geo.max_seq);
-        sx_exact<D, G, NW>(geo, d, u, n, L.sel, max(0, min(d.eb, L.nsel)), 0, L);
-    } else {
-        const int n_raw = d.seq_lens[u / geo.hkv];
-        const int e0 = w * d.eb;
-        const int nblk = max(0, min(d.eb, a.K - e0));  // (the ids past n_sel are -1)
+    bool selects = w == 0;  // (workgroup-uniform)
+    bool comp = false;      // a compensation partial waits in LDS
+    int n_raw = 0, nblk = 0;
+    const int e0 = w * d.eb;
+    if (w != 0) {
+        n_raw = d.seq_lens[u / geo.hkv];
+        nblk = max(0, min(d.eb, a.K - e0));  // (the ids past n_sel are -1)
         uint32_t mv = 0u;
         auto request = [&] { mv = ld_agent_u32(mbox + (tid < nblk ? e0 + tid : 0)); };
-        const bool comp = d.n_comp > 0;  // (workgroup-uniform)
+        comp = d.n_comp > 0;
         if (comp) {  // its compensation partial stays in LDS for the exact partial to absorb
             // the 512-thread form is bound by the bytes of many short sequences: equal shares of the
             // sequence's own blocks (ragged lengths: 74 -> 60 us a step at 256 units of 1K-8K tokens).
@@ -193,28 +187,48 @@ __global__ __launch_bounds__(FT) void select_work_kernel(Geom geo, ScoreArgs a, 
         } else {
             request();
         }
-        const int n = clamp_len(n_raw, geo.max_seq);
-        bool ok = true;
-        if (tid < nblk) {
-            for (int spins = 0; mv == 0u && spins < kSelSpinLimit; ++spins) {
-                __builtin_amdgcn_s_sleep(2);
-                mv = ld_agent_u32(mbox + e0 + tid);
+        static_assert(kMaxEb <= 128, "waves 0 and 1 hold the ids");
+        if (tid < 128) {
+            bool missed = false;
+            if (tid < nblk) {
+                for (int polls = 0; mv == 0u && polls < d.polls; ++polls) {
+                    __builtin_amdgcn_s_sleep(2);
+                    mv = ld_agent_u32(mbox + e0 + tid);
+                }
+                missed = mv == 0u;
+                L.sel[tid] = (int32_t)(mv ^ kPosted);
             }
-            ok = mv != 0u;
-            L.sel[tid] = ok ? (int32_t)(mv ^ kPosted) : -1;
-        }
-        if (!ok) {
-            __hip_atomic_fetch_or(word, kSelFailed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            if (d.timeouts) __hip_atomic_fetch_add(d.timeouts + 4 * u + 3, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            missed = __any(missed);
+            if ((tid & 63) == 0) {
+                L.missed[tid >> 6] = missed;
+                if (missed && d.timeouts)
+                    __hip_atomic_fetch_add(d.timeouts + 4 * u + 3, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
         }
         __syncthreads();
-        COMPKV_MARK(d.trace, 7);  // the ids in hand
-        sx_exact<D, G, NW>(geo, d, u, n, L.sel, nblk, w, L, comp);
+        selects = (L.missed[0] | L.missed[1]) != 0;
     }
+    if (selects) {
+        finalize_select<G, false, FT, KPT, kLogits>(geo, a, u, L.u.fin, dyn, L.sel, &L.nsel, w == 0);
+        __syncthreads();
+    }
+    if (w == 0) {
+        COMPKV_MARK(d.trace, 4);  // selected
+        for (int k = tid; k < a.K; k += FT) {
+            const int32_t b = L.sel[k];
+            st_agent_u32(mbox + k, (uint32_t)b ^ kPosted);
+            a.sel[(size_t)u * a.K + k] = b;
+        }
+        if (tid == 0) a.n_sel[u] = L.nsel;
+        n_raw = d.seq_lens[u / geo.hkv];
+        nblk = max(0, min(d.eb, L.nsel));
+    } else {
+        COMPKV_MARK(d.trace, 7);  // the ids in hand
+    }
+    sx_exact<D, G, NW>(geo, d, u, clamp_len(n_raw, geo.max_seq), selects ? L.sel + e0 : L.sel, nblk, w, L, comp);
     if (arrive_last(d.arrive + u, P, L.last)) {
         COMPKV_MARK(d.trace, 10);  // this workgroup merges
-        const bool failed = (ld_agent_u32(word) & kSelFailed) != 0;  // (workgroup-uniform)
-        merge_unit<D, G, Lds, FT>(geo, d, u, L, failed);
+        merge_unit<D, G, Lds, FT>(geo, d, u, L);
     }
     COMPKV_TRACE_END(d.trace);
 }
@@ -295,6 +309,7 @@ hipError_t sx_g(const Geom& g, const ScoreArgs& a, const DecodeArgs& d, int item
 
 }  // namespace
 
+int select_poll_limit() { return kSelPollLimit; }
 int select_exact_max_budget() { return kSelLdsMax; }
 int select_exact_waves() { return kSxThreads / 64; }
 int select_exact_max_cb() { return kStepCbMax; }
@@ -357,7 +372,7 @@ hipError_t launch_select_work(const Geom& g, ScoreArgs a, const DecodeArgs& d, i
     const int keff = std::max(1, std::min(a.K, g.xmax()));
     if (P < 2 || a.bpc < 1 || (a.bpc & (a.bpc - 1)) != 0 || g.xmax() > kFinThreads * kKeysPerThread || a.K > kSelLdsMax ||
         d.eb < 1 || d.eb > kMaxEb || (long long)P * d.eb < keff || finalize_dyn_lds(g, a) > kDynBudget || !d.arrive ||
-        !d.sel_word || !d.mailbox ||
+        !d.mailbox ||
         (d.n_comp != 0 && (d.n_comp != P - 1 || d.cb < 1 || d.cb > kStepCbMax || (long long)d.n_comp * d.cb < g.xmax())) ||
         d.part_base != 0 || d.part_count != P || d.part_count * g.G > kMergeMaxTerms)
         return hipErrorInvalidValue;

@@ -121,8 +121,8 @@ struct ScoreArgs {
     int score_kind;         // COMPKV_SCORE_*: CompKV score, mass only, or first-order mass estimate
     int chunks_only;        // chunked path: launch the chunk scoring without the selection
     int tail_first;         // set by the launcher: the last-block workgroups lead the grid (else trail)
-    uint32_t* arrive_zero;  // nullable: [2][units] words (arrivals, selection words), then [units][K]
-                            // (mailbox), that the last-block workgroups zero
+    uint32_t* arrive_zero;  // nullable: [units] words (arrivals), then [units][K] (mailbox), that the
+                            // last-block workgroups zero
     unsigned long long* trace;  // phase-trace build only: [grid][kTraceSlots] timestamps, or null
 };
 
@@ -154,8 +154,8 @@ struct DecodeArgs {
     uint32_t* arrive;  // fused selection/exact launch: per-unit arrival counters (zeroed by the chunk
                        // launch); the unit's last workgroup merges its partials (null: a merge launch
                        // follows)
-    uint32_t* sel_word;  // one-selector fused launch: per-unit selection words (zeroed by the chunk launch)
     uint32_t* mailbox;   // one-selector fused launch: [units][K] posted ids (zeroed by the chunk launch)
+    int polls;           // one-selector fused launch: polls of a worker's wait before it selects itself
     uint32_t* timeouts;  // per-unit words [units][4] at the start of the workspace (word 3 counts timeouts)
     unsigned long long* trace;  // phase-trace build only: [grid][kTraceSlots] timestamps, or null
 };
@@ -190,6 +190,7 @@ hipError_t launch_select_exact(const Geom& g, ScoreArgs a, const DecodeArgs& d, 
 // worker's compensation partial joins its exact one); workgroups of `threads` (1024 or 512) threads;
 // hipErrorInvalidValue outside its limits
 hipError_t launch_select_work(const Geom& g, ScoreArgs a, const DecodeArgs& d, int P, int threads, hipStream_t s);
+int select_poll_limit();  // polls of a worker's wait in the one-selector form
 int select_exact_max_budget();
 int select_exact_waves();
 int select_exact_max_cb();  // blocks per compensation workgroup of the fused launch

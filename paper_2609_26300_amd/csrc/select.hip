@@ -106,11 +106,8 @@ __device__ void score_tail(const Geom& geo, const ScoreArgs& a, int u, TailShare
     const int X = (n + geo.B - 1) / geo.B;
     float* pp = a.ws_part + ((size_t)u * (nc + 1) + nc) * G * 2;
     if (a.arrive_zero) {  // for the launch that merges after this one
-        if (tid == 0) {
-            a.arrive_zero[u] = 0u;
-            a.arrive_zero[geo.units() + u] = 0u;
-        }
-        uint32_t* mbox = a.arrive_zero + 2 * (size_t)geo.units() + (size_t)u * a.K;
+        if (tid == 0) a.arrive_zero[u] = 0u;
+        uint32_t* mbox = a.arrive_zero + (size_t)geo.units() + (size_t)u * a.K;
         for (int k = tid; k < a.K; k += kThreads) mbox[k] = 0u;
     }
     // fused step with Mean compensation: this workgroup's compensation partial

@@ -586,6 +586,7 @@ struct SelExactLdsT {
     float cw[G][CB];          // compensation workgroups: pseudo-logits, then their weights
     float cm[G], cl[G];
     int32_t last;             // this workgroup arrived last for its unit (it merges the partials)
+    int32_t missed[2];        // one-selector form: ids that waves 0 and 1 waited for were not posted in time
 };
 template <int D, int G>
 using SelExactLds = SelExactLdsT<D, G, kStepCbMax>;
