@@ -142,8 +142,8 @@ typedef struct compkv_select_params {
  *   AUTO:      in compkv_score_select, ONE_GROUP when a unit holds at most 256 blocks (one workgroup
  *              then reads every summary in a single round of loads), else CHUNKED. In
  *              compkv_decode_step, CHUNKED_EXACT when all of its workgroups are resident at once (one
- *              of 1024 or two of 512 threads per compute unit), else ONE_GROUP when a unit holds at most 256 blocks, else
- *              CHUNKED.
+ *              of 1024 or two of 512 threads per compute unit), else ONE_GROUP when a unit holds at most
+ *              256 blocks, else CHUNKED.
  */
 #define COMPKV_SELECT_AUTO 0
 #define COMPKV_SELECT_CHUNKED 1
@@ -297,6 +297,11 @@ int compkv_select_polls_set(int polls);
  * COMPKV_SELECT_ONE_GROUP, COMPKV_SELECT_CHUNKED or COMPKV_SELECT_CHUNKED_EXACT (params->select_path
  * resolved), or a negative status (invalid dims or path). Enqueues nothing. */
 int compkv_decode_step_path(const compkv_dims* dims, const compkv_select_params* params);
+
+/* The form of that shape's fused selection/exact launch: *threads receives the threads of its workgroups (1024 or 512; 0
+ * where the shape is not COMPKV_SELECT_CHUNKED_EXACT) and *workgroups the workgroups per unit of its one-selector form
+ * (0: the form of item and compensation workgroups). Returns COMPKV_OK or as compkv_decode_step_path. Enqueues nothing. */
+int compkv_decode_step_form(const compkv_dims* dims, const compkv_select_params* params, int* threads, int* workgroups);
 
 /*
  * Offload tier (Appendix E.1 keeps the cache in host memory): k_cache and v_cache may live in pinned,

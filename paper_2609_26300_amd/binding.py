@@ -115,6 +115,9 @@ def library():
         L.compkv_decode_step_noalloc_limit.argtypes = []
         L.compkv_decode_step_noalloc_limit.restype = ctypes.c_size_t
         L.compkv_decode_step_path.argtypes = [dp, ctypes.POINTER(CompkvSelectParams)]
+        L.compkv_decode_step_form.argtypes = [dp, ctypes.POINTER(CompkvSelectParams), ctypes.POINTER(ctypes.c_int),
+                                              ctypes.POINTER(ctypes.c_int)]
+        L.compkv_decode_step_form.restype = ctypes.c_int
         L.compkv_phase_trace_set.argtypes = [_vp, _vp]
         L.compkv_phase_trace_set.restype = ctypes.c_int
         L.compkv_select_polls_set.argtypes = [_i32]
@@ -290,6 +293,15 @@ def compkv_decode_step_path(dims: CompkvDims, params: CompkvSelectParams) -> int
     st = library().compkv_decode_step_path(ctypes.byref(dims), ctypes.byref(params))
     _check(st if st < 0 else 0, "compkv_decode_step_path")
     return int(st)
+
+
+def compkv_decode_step_form(dims: CompkvDims, params: CompkvSelectParams) -> tuple[int, int]:
+    """Threads of the fused selection/exact launch's workgroups (0: no such launch) and, in its one-selector form, the
+    workgroups per unit (0: item and compensation workgroups)."""
+    threads, workgroups = ctypes.c_int(), ctypes.c_int()
+    _check(library().compkv_decode_step_form(ctypes.byref(dims), ctypes.byref(params), ctypes.byref(threads),
+                                             ctypes.byref(workgroups)), "compkv_decode_step_form")
+    return threads.value, workgroups.value
 
 
 def compkv_workspace_bytes(dims: CompkvDims, budget_blocks: int, which: int = COMPKV_WS_ALL) -> int:

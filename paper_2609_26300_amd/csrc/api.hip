@@ -164,7 +164,7 @@ struct SxShape {  // the fused step's selection + exact launch (sx_shape below)
     int eb, n_exact;
     int cb, n_comp;  // its compensation workgroups: blocks each, workgroups per unit
     bool fits;       // within the kernel's limits
-    bool one_round;  // every workgroup of the chosen form resident at once (one per CU)
+    bool one_round;  // every workgroup of the chosen form resident at once
     bool work;       // the one-selector form (below) is chosen
     int wt;          // one-selector form: threads of a workgroup
     int P, web, wcb;  // one-selector form: workgroups per unit, exact blocks each, compensation blocks
@@ -279,7 +279,8 @@ SxShape sx_shape(const Geom& g, int nchunks, int K) {
     // The 512-thread form serves
     //  * more than half as many units as CUs, so that a unit keeps its worker and one workgroup's loads
     //    overlap the other's selection (256 units of up to 8K tokens: 61 us a step against 78 for the four
-    //    separate launches; 160 units 51 against 59);
+    //    separate launches; 160 units 51 against 59). Past one unit per CU two workgroups each no longer fit,
+    //    and the step is the four launches;
     //  * units of up to 2048 blocks, whose step is a chain of short phases that eight waves pass through
     //    faster than sixteen, with more workgroups per unit (below; us a step, 1024 / 512 threads: 8 units
     //    of 32K tokens in 1024 blocks 24.9 / 22.3, of 16K in 512 25.3 / 21.5, of 64K in 2048 25.3 / 23.2,
@@ -643,6 +644,20 @@ int compkv_decode_step_path(const compkv_dims* dims, const compkv_select_params*
     if (!params) return COMPKV_EINVAL;
     const int path = step_path(g, params, &st);
     return st != COMPKV_OK ? st : path;
+}
+
+int compkv_decode_step_form(const compkv_dims* dims, const compkv_select_params* params, int* threads, int* workgroups) {
+    if (!threads || !workgroups) return COMPKV_EINVAL;
+    *threads = *workgroups = 0;
+    const int path = compkv_decode_step_path(dims, params);
+    if (path < 0) return path;
+    if (path != COMPKV_SELECT_CHUNKED_EXACT) return COMPKV_OK;
+    Geom g;
+    check_dims(dims, &g);
+    const SxShape sx = sx_shape(g, score_shape(g).nchunks, params->budget_blocks);
+    *threads = sx.work ? sx.wt : 64 * compkv::select_exact_waves();
+    *workgroups = sx.work ? sx.P : 0;
+    return COMPKV_OK;
 }
 
 int compkv_decode_step(const compkv_dims* dims, const compkv_select_params* params, const void* q, void* k_cache,

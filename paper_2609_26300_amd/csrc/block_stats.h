@@ -1,5 +1,5 @@
 // block_stats.h -- the block summary routine shared by the prefill, the append and the fused decode
-// step (private to libcompkv). Every caller runs the same workgroup-wide routine, so a summary does not
+// step (private to libcompkv): a workgroup's and a wave's, which add in the same order, so a summary does not
 // depend on which of them computed it (Section 4.2: an appended block's summary equals a rebuild).
 #pragma once
 
@@ -30,7 +30,7 @@ struct BlockStatsLds : BlockMeansLds<D> {
 // four times that. Wave w takes rows 16s + 4w + (lane / 16) (for d = 128) of each step s, up to four
 // steps per batch with every load of a batch issued before use. Per-lane sums over the rows, then the
 // four waves' sums of each row group ((w0 + w1) + (w2 + w3)), then the row groups pairwise
-// ((g0 + g1) + (g2 + g3), ...): the order in which one wave that plays all four (wave_block_stats) needs
+// ((g0 + g1) + (g2 + g3), ...): the order in which one wave that plays all four (build_stats_wave_kernel) needs
 // a single butterfly over its lanes instead of one per wave played. Two passes (mean, then
 // squared deviations from the mean) keep the variance stable; a block of at most one batch per wave
 // (64 rows for d = 128) is still in registers for the second pass. On return the results are written
@@ -196,8 +196,8 @@ __device__ void block_stats_from(const BlockSrc& b, BlockRows& R, int r, int lay
 // steps (NS * 4 * 64/(d/8) rows). The wave plays the four waves of the workgroup routine (virtual wave v
 // takes the rows the real wave v takes there) and adds in exactly the same order: per lane over the steps,
 // the four waves' sums, the butterflies over the row groups, the pair sums and the group butterflies over
-// lanes = pairs. So its results are bit-identical to block_stats_from's, which the append and the fused
-// step keep using.
+// lanes = pairs. So its results are bit-identical to block_stats_from's, which the append and the fused step
+// keep using, also where rows hold infinities or NaNs (which NaN aside).
 template <int D>
 constexpr int wave_stats_max_rows(int steps) {
     return steps * 4 * (64 / (D / 8));

@@ -185,8 +185,8 @@ hipError_t launch_decode_items(const Geom& g, const DecodeArgs& a, int items, hi
 // its limits
 hipError_t launch_select_exact(const Geom& g, ScoreArgs a, const DecodeArgs& d, int items, hipStream_t s);
 // the same step with one selector per unit and P - 1 workers (compensation share d.cb, then exact share
-// d.eb once the selection word is set): P workgroups per unit, all resident at once (checked by the
-// caller with select_exact_slots); one partial per workgroup (d.part_count = P, d.part_base = 0: a
+// d.eb once its ids are posted): P workgroups per unit, all resident at once on an otherwise idle GPU (checked by
+// the caller with select_exact_slots; what follows otherwise stands at the kernel); one partial per workgroup (d.part_count = P, d.part_base = 0: a
 // worker's compensation partial joins its exact one); workgroups of `threads` (1024 or 512) threads;
 // hipErrorInvalidValue outside its limits
 hipError_t launch_select_work(const Geom& g, ScoreArgs a, const DecodeArgs& d, int P, int threads, hipStream_t s);

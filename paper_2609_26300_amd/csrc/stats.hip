@@ -1,9 +1,9 @@
 // stats.hip -- block summaries: prefill build and streaming append (Sections 4.1, 4.2; Appendix E.1).
 //
-// The prefill strides over every (unit, block): one wave per block up to 64 rows at d = 128, else one
-// workgroup (wg_block_stats, block_stats.h). The append recomputes each unit's active block with the workgroup
-// routine after storing the new row, like the fused decode step. Wave and workgroup add in the same order,
-// so an appended block's summary is bit-identical to the prefill one.
+// The prefill strides over every (unit, block): one wave per block up to 64 rows at d = 128 (from 33 rows on
+// while the blocks occupy every wave of a round), else one workgroup (wg_block_stats, block_stats.h). The append
+// recomputes each unit's active block with the workgroup routine after storing the new row, like the fused decode
+// step. Wave and workgroup add in the same order, so an appended block's summary is bit-identical to the prefill one.
 #include "block_stats.h"
 
 namespace compkv {

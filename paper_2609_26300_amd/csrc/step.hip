@@ -33,8 +33,8 @@
 // Handoffs inside launch 2 use device-coherent stores and loads (relaxed atomics at agent scope: they
 // bypass the per-XCD caches), each thread's stores completed before its workgroup's arrival is
 // counted or the ids are published. The only wait (an exact workgroup for its unit's ids) is on a
-// selector, which has a lower id and never waits, so under the in-order dispatch of workgroups every
-// wait ends; it is also bounded: on a timeout the unit is marked, its outputs become NaN and the
+// selector, which has a lower id and never waits, so where workgroups start in order across the GPU every
+// wait ends (another stream's workgroups may hold an XCD on which a selector still queues); it is also bounded: on a timeout the unit is marked, its outputs become NaN and the
 // unit's timeout word counts it, so the launch always drains.
 #include "select_core.h"
 

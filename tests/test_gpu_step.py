@@ -247,13 +247,14 @@ def test_step_stays_within_workspace(name, path):
 # the fused launch's 512-thread form: more than half as many units as compute units (two or three workgroups per
 # unit), on lengths from empty to full, with a budget above the shortest sequences' blocks, G = 8 and unit
 # counts that do not fill whole rounds of eight; and few short units (up to 20 workgroups each) at the edges of its
-# keys per thread (512, 1024 and 2048 blocks) and of the 1024-thread form past them
+# keys per thread (512, 1024 and 2048 blocks) and of the 1024-thread form past them; the form is asked for and checked
 @pytest.mark.parametrize("batch,heads,d,B,context,budget", [(65, (8, 2), 128, 16, 1030, 12), (70, (16, 2), 64, 48, 2500, 20),
                                                             (129, (1, 1), 128, 1, 700, 130), (128, (4, 2), 128, 32, 900, 9),
                                                             (1, (8, 2), 128, 1, 512, 200), (1, (8, 2), 128, 1, 513, 40),
                                                             (1, (4, 4), 64, 1, 1024, 33), (2, (8, 1), 128, 1, 1025, 130),
                                                             (1, (2, 1), 128, 1, 2048, 300), (1, (4, 1), 128, 1, 2049, 40),
-                                                            (1, (16, 2), 128, 2, 2047, 24), (6, (8, 2), 64, 16, 4000, 60)])
+                                                            (1, (16, 2), 128, 2, 2047, 24), (6, (8, 2), 64, 16, 4000, 60),
+                                                            (130, (8, 1), 64, 1, 1500, 30), (65, (4, 2), 128, 1, 1500, 40)])
 def test_step_small_workgroups(batch, heads, d, B, context, budget):
     lens = [context, 0, 1, B, B + 1, context - 1] + [1 + (37 * i) % context for i in range(6, batch)]
     lens = lens[:batch]
@@ -264,6 +265,14 @@ def test_step_small_workgroups(batch, heads, d, B, context, budget):
     ref = c.decode_step()
     c.select_path = P.COMPKV_SELECT_AUTO
     assert P.compkv_decode_step_path(c.dims, c.params()) == P.COMPKV_SELECT_CHUNKED_EXACT
+    units, blocks = batch * heads[1], -(-context // B)
+    many = 2 * units > torch.cuda.get_device_properties(0).multi_processor_count
+    few_heads = heads[0] // heads[1] < 8
+    small = blocks <= 2048 and (many or few_heads or (blocks <= 1024 and units <= 32))
+    threads, workgroups = P.compkv_decode_step_form(c.dims, c.params())
+    assert threads == (512 if small else 1024)
+    if small:
+        assert workgroups >= 2 and (not many or workgroups <= 3) and (workgroups >= 3 or blocks <= 1024)
     K2, V2, kn, vn, summ2 = _prefix_state(c)
     got = c.decode_step(kn, vn, summ=summ2, K=K2, V=V2)
     torch.cuda.synchronize()
