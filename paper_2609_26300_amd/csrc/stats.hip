@@ -57,12 +57,12 @@ __global__ __launch_bounds__(kThreads) void build_stats_kernel(Geom g, StatsArgs
 // HBM-bound, with the vector ALUs ~40% busy: the wave holds the block's keys (needed twice) and its values, VS
 // steps at a time; the next block's values are requested as soon as this block's are added and its keys as
 // soon as the squared deviations are, so loads stay in flight while the wave computes (the registers are loaded in
-// place). With the masks as factors, one butterfly per sum and
-// the exact reciprocal of a power-of-two count a block takes 890 vector instructions. One layer of 32K tokens
-// x 8 KV heads, d = 128, blocks of 32: 39.1 -> 29.3 us (143 MB, 4.9 TB/s); 128K x 4: 490 -> 403 us (5.7 TB/s);
-// blocks of 16: 923 -> 430 us; d = 64: 532 -> 206 us. The test for sums that are not finite (partly filled blocks
-// alone) costs up to 3%; clearing each row past a block instead cost up to 12%. (Five workgroups per CU asked for:
-// without it the recomputation after the loop takes the small form's registers past that.)
+// place). With the masks as factors, one butterfly per sum and the exact reciprocal of a power-of-two count a
+// block takes 890 vector instructions. One layer of 32K tokens x 8 KV heads, d = 128, blocks of 32: 39.1 -> 27.6 us
+// (143 MB, 5.2 TB/s); 128K x 4: 490 -> 443 us (5.2 TB/s); 131072 blocks of 16: 469 -> 216 us, at d = 64 516 -> 157.
+// The test for sums that are not finite (partly filled blocks alone) costs up to 3%; clearing each row past a block
+// instead cost up to 12%. (Five workgroups per CU asked for: without it the recomputation after the loop takes the
+// small form's registers past that.)
 // After a wave's last block its first row is requested once more, unused, so that no branch lies around the loads; with
 // the whole block requested again a build of 2048 blocks took 11.9 us against 10.4 and one of 32K from host memory 3.02 ms
 // against 2.48.
