@@ -282,3 +282,29 @@ def test_step_small_workgroups(batch, heads, d, B, context, budget):
     for k in ("sel", "n_sel", "blk_logit", "scores"):
         assert torch.equal(got[k], ref[k]), k
     _oracle_end_to_end(c, got)
+
+
+@pytest.mark.parametrize("heads,d,batches", [((8, 2), 128, (65, 18)), ((12, 12), 64, (3, 11))])
+def test_two_streams_at_once(heads, d, batches):
+    """Steps on two streams, each with a workspace of its own, unit counts that spread a unit's workgroups over the
+    XCDs and launches that each fill the GPU: every step's outputs are those of the step alone."""
+    cases = []
+    for i, batch in enumerate(batches):
+        c = Case(TINY.with_(batch=batch, n_q_heads=heads[0], n_kv_heads=heads[1], head_dim=d, block_size=16,
+                            context=1500, budget_blocks=20, seed=63 + i), seq_lens=[1500 - 17 * (j % 60) for j in range(batch)])
+        c.build_stats()
+        assert P.compkv_decode_step_form(c.dims, c.params())[1] >= 2 and batch * heads[1] % 8
+        cases.append((c, c.decode_step(), torch.cuda.Stream()))
+    torch.cuda.synchronize()
+    outs = []
+    for rep in range(40):
+        for c, _, s in cases:
+            with torch.cuda.stream(s):
+                outs.append((c, c.decode_step()))
+        if rep % 10 == 9:
+            torch.cuda.synchronize()
+    torch.cuda.synchronize()
+    for c, got in outs:
+        ref = next(r for x, r, _ in cases if x is c)
+        for k in ("sel", "n_sel", "blk_logit", "out", "lse"):
+            assert torch.equal(got[k], ref[k]), k
